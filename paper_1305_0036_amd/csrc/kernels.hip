@@ -14,8 +14,9 @@
 //   sweep_pipe_kernel  the same stages with a grid of resident workgroups that prefetch
 //                      their next tile into a second register set.
 //   sweep_kernel       the same pass with the tile staged in LDS (kept for tuning).
-//   resident_kernel    a state that fits one tile: a whole recording segment in LDS, one
-//                      workgroup per state (or per chain of a batch).
+//   resident_kernel    a state that fits one workgroup's registers: a whole recording
+//                      segment in one launch, one workgroup per state (or per chain of a
+//                      batch).
 //   reduce_kernel, batch_reduce_kernel, finalize_kernel
 //                      FP64 observables of Sec. 4.2 (norm, spin components, correlations,
 //                      magnetisation, overlaps) and the energy <H> of Eq. 1, with a
@@ -1763,132 +1764,325 @@ __global__ __launch_bounds__(1 << (T - RB)) void sweep_pipe_kernel(typename Vec<
     }
 }
 
-// Whole-state kernel: one workgroup per vector runs every (phase, layer) pass of a segment.
-// For n < 8 the T = 8 instance is used with only 2^n amplitudes live.
-__device__ __forceinline__ double wave_sum(double v);
+// ------------------------------------------------------------------ resident states
+//
+// A state that fits the registers of one workgroup (N <= 13, complex64 14): the whole
+// segment in one launch.  One workgroup on one CU waits for no memory: its time is the
+// layers' arithmetic and the exchange of amplitudes between threads, one layer after the
+// other.  Each thread holds 2^RB amplitudes along a window of RB index bits, as in the
+// register sweeps; a layer visits the windows from the highest to the lowest, the next layer
+// from the lowest to the highest, so a layer of W windows needs W - 1 transposes through LDS
+// and the phase steps run at the two end windows (complex64: always from the lowest, W
+// transposes; see resident_ascending).  Windows, masks and LDS offsets are known when
+// compiling.  Up to 64 threads (N <= 9) the workgroup is one wave, whose LDS operations are
+// in order without barriers.
+//
+// Measured, per fourth-order step (20 layers) of one complex128 vector: N = 12 180 -> 48 us,
+// N = 9 56 -> 17 us against the state kept in LDS (three bits per pass and a barrier after
+// each).  A layer at N = 12 is then 5800 cycles: 3072 of LDS (three transposes of 64 KB each
+// way at 128 bytes a cycle), 2000 of vector arithmetic, and latency at the barriers.  Eight
+// amplitudes per thread (512 threads, two waves per SIMD) instead of sixteen: 48 against
+// 53 us at N = 12, 25 against 31 at N = 10, although a layer then takes one transpose more.
+// Real and imaginary parts exchanged apart, so that one part's butterflies run while the
+// other is under way: 55 us (8-byte LDS accesses move half the bytes per cycle of 16-byte
+// ones).
 
-// FP64 observables of the LDS-resident state (real kinds: norm, S^x, S^y, S^z of a spin,
-// S^z S^z, M^z), written to out[slot].  Every thread of the workgroup calls it.
-template <typename V>
-__device__ void resident_record(const V *tile, int ne, int n, const ObsDev *obs, int n_obs,
-                                double *out)
+// Phase tables (resident_phase_entries): for the thread's bits outside the window, with every
+// window bit down, th[0] = kappa i^(c popcount) exp(-i tau E); per window bit th[1 + v] =
+// exp(-i tau g_v), the factor that flips it up; and the table over the window's bits of its
+// own couplings and quarter turns.  Block (phase, chain), one thread per thread pattern.
+__global__ void resident_phase_kernel(ResidentPhaseArgs a)
 {
-    __shared__ double red[kThreads / 64][kMaxObs];
-    double acc[kMaxObs];
-#pragma unroll
-    for (int o = 0; o < kMaxObs; ++o) acc[o] = 0.0;
-    for (int t = threadIdx.x; t < ne; t += kThreads) {
-        const V c = tile[t];
-        const double cr = c.x, ci = c.y, p = cr * cr + ci * ci;
-#pragma unroll
-        for (int o = 0; o < kMaxObs; ++o) {
-            if (o >= n_obs) continue;
-            const ObsDev ob = obs[o];
-            switch (ob.kind) {
-            case 0: acc[o] += p; break;
-            case 3: acc[o] += (((t >> ob.i) & 1) ? 0.5 : -0.5) * p; break;
-            case 4: acc[o] += ((((t >> ob.i) ^ (t >> ob.j)) & 1) ? -0.25 : 0.25) * p; break;
-            case 5: acc[o] += ((double)__builtin_popcount(t) - 0.5 * n) * p; break;
-            case 1:
-            case 2:
-                if (!((t >> ob.i) & 1)) {
-                    const V u = tile[t | (1 << ob.i)];
-                    const double zr = cr * u.x + ci * u.y, zi = cr * u.y - ci * u.x;
-                    acc[o] += (ob.kind == 1) ? zr : -zi;
+    const int n = a.n, T = n < 8 ? 8 : n, RB = resident_reg_bits(n), nt = 1 << (n - RB);
+    const ResidentPhase ph = a.phases[blockIdx.x];
+    const int w = ph.top ? n - RB : 0, tid = threadIdx.x;
+    const int ax = ph.d.axis;
+    const double *wg = nullptr, *jt = nullptr;
+    if (ax >= 0 && ax < 3) {
+        wg = a.chains ? a.chains[blockIdx.y].wg[ax] : a.wg[ax];
+        jt = a.chains ? a.chains[blockIdx.y].jt[ax] : a.jt[ax];
+    }
+    double2 *out = reinterpret_cast<double2 *>(a.tab) +
+                   ((size_t)blockIdx.y * a.n_phases + blockIdx.x) * resident_phase_entries(n);
+    const uint32_t t0 = (tid & ((1u << w) - 1u)) | (((uint32_t)tid >> w) << (w + RB));
+    auto spin = [&](uint32_t b, int k) { return ((b >> k) & 1u) ? 0.5 : -0.5; };
+    auto inside = [&](int k) { return k >= w && k < w + RB; };
+    if (tid < nt) {
+        double E = wg ? wg[0] : 0.0, g[kRegBits] = {0.0, 0.0, 0.0, 0.0};
+        if (wg) {
+            for (int k = 0; k < n; ++k) {
+                if (inside(k)) {
+                    g[k - w] += wg[1 + k];
+                    continue;
                 }
-                break;
-            default: break;
+                E += spin(t0, k) * wg[1 + k];
+                for (int m = k + 1; m < n; ++m)
+                    if (!inside(m)) E += spin(t0, k) * spin(t0, m) * jt[k * T + m];
+            }
+            for (int v = 0; v < RB; ++v) {
+                for (int k = 0; k < n; ++k)
+                    if (!inside(k)) g[v] += spin(t0, k) * jt[k < w ? k * T + w + v : (w + v) * T + k];
+                E -= 0.5 * g[v];
             }
         }
+        out[tid] = qturn(cmul(make_double2(ph.d.kre, ph.d.kim), expi(-ph.d.tau * E)), ph.d.qturn * __popc(t0));
+        for (int v = 0; v < RB; ++v) out[(1 + v) * nt + tid] = expi(-ph.d.tau * g[v]);
     }
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-    for (int o = 0; o < kMaxObs; ++o) {
-        if (o >= n_obs) continue;
-        const double s = wave_sum(acc[o]);
-        if (lane == 0) red[wv][o] = s;
+    if (tid < (1 << RB)) {
+        double Q = 0.0;
+        if (wg)
+            for (int v = 0; v < RB; ++v)
+                for (int u = v + 1; u < RB; ++u)
+                    Q += spin(tid, v) * spin(tid, u) * jt[(w + v) * T + w + u];
+        out[(1 + RB) * nt + tid] = qturn(expi(-ph.d.tau * Q), ph.d.qturn * __popc((uint32_t)tid));
     }
-    __syncthreads();
-    if (threadIdx.x < n_obs) {
-        double s = 0.0;
-        for (int w = 0; w < kThreads / 64; ++w) s += red[w][threadIdx.x];
-        out[obs[threadIdx.x].slot] = s;
-    }
-    __syncthreads();
 }
 
-template <typename R, int T>
-__global__ __launch_bounds__(kThreads) void resident_kernel(ResidentArgs a)
+// Orders this workgroup's LDS operations; one wave's are in order by themselves.
+template <int NT>
+__device__ __forceinline__ void resident_barrier()
 {
+    if constexpr (NT > 64)
+        lds_barrier();
+    else
+        asm volatile("" ::: "memory");
+}
+
+// The exchange buffer.  With two halves used in turn (B2 > 0: the offset of the other one) a
+// transpose writes the half that the one before the last wrote: the barrier between has seen
+// every wave past its reads, so one barrier per transpose is enough and its writes can start
+// while the layer before still computes.
+template <typename V, int B2>
+struct ResidentLds {
+    V *buf;
+    bool odd;
+    __device__ __forceinline__ V *next()
+    {
+        if constexpr (B2 == 0) return buf;
+        odd = !odd;
+        return buf + (odd ? B2 : 0);
+    }
+};
+
+template <int NT, int RB, int FROM, int TO, typename V, int B2>
+__device__ __forceinline__ void resident_transpose(V (&x)[1 << RB], ResidentLds<V, B2> &l)
+{
+    const uint32_t tid = threadIdx.x;
+    V *lds = l.next();
+    V *pf = lds + lds_pos(thread_part<RB>(tid, FROM)), *pt = lds + lds_pos(thread_part<RB>(tid, TO));
+    if constexpr (B2 == 0) resident_barrier<NT>();
+#pragma unroll
+    for (int r = 0; r < (1 << RB); ++r) pf[lds_pos((uint32_t)r << FROM)] = x[r];
+    resident_barrier<NT>();
+#pragma unroll
+    for (int r = 0; r < (1 << RB); ++r) x[r] = pt[lds_pos((uint32_t)r << TO)];
+}
+
+// Butterflies on the bits of window K that no lower window holds, then the windows below
+// (DOWN) or above it.
+template <int N, int RB, int K, bool DOWN, typename V, int B2>
+__device__ __forceinline__ void resident_layer(V (&x)[1 << RB], ResidentLds<V, B2> &lds)
+{
+    constexpr int NW = (N + RB - 1) / RB, NT = 1 << (N - RB);
+    constexpr int W = K * RB < N - RB ? K * RB : N - RB;
+    reg_bfly<RB>(x, ((1u << RB) - 1u) & ~((1u << (K * RB - W)) - 1u));
+    constexpr int K2 = DOWN ? K - 1 : K + 1;
+    if constexpr (K2 >= 0 && K2 < NW) {
+        constexpr int W2 = K2 * RB < N - RB ? K2 * RB : N - RB;
+        resident_transpose<NT, RB, W, W2>(x, lds);
+        resident_layer<N, RB, K2, DOWN>(x, lds);
+    }
+}
+
+// Factor of register j: th[0], the factors of its set bits (the highest bit first: few
+// products are alive at a time), the window table.  use(j, factor) takes them.
+template <int RB, int V, typename F>
+__device__ __forceinline__ void resident_phase(double2 p, int j, const double2 (&th)[1 + RB], ctab q, F use)
+{
+    if constexpr (V == 0) {
+        use(j, cmul(p, ld2(q, j)));
+    } else {
+        resident_phase<RB, V - 1>(p, j, th, q, use);
+        resident_phase<RB, V - 1>(cmul(p, th[V]), j | (1 << (V - 1)), th, q, use);
+    }
+}
+
+// The factors of the phase tables, register-major: block = phase.
+template <int N>
+__global__ __launch_bounds__(resident_threads(N)) void resident_factor_kernel(const double *tab, double *fac)
+{
+    constexpr int RB = resident_reg_bits(N), NT = 1 << (N - RB);
+    const double2 *t = reinterpret_cast<const double2 *>(tab) + (size_t)blockIdx.x * resident_phase_entries(N);
+    double2 *out = reinterpret_cast<double2 *>(fac) + ((size_t)blockIdx.x << N);
+    double2 th[1 + RB];
+#pragma unroll
+    for (int v = 0; v <= RB; ++v) th[v] = t[v * NT + threadIdx.x];
+    const ctab q = as_const(reinterpret_cast<const double *>(t + NT * (1 + RB)));
+    resident_phase<RB, RB>(th[0], 0, th, q, [&](int j, double2 z) { out[j * NT + threadIdx.x] = z; });
+}
+
+// FP64 observables of the state in registers (window w; real kinds: norm, S^x, S^y, S^z of a
+// spin, S^z S^z, M^z), written to out[slot].  S^x and S^y read the flipped partner from LDS.
+template <int N, int RB, typename V>
+__device__ void resident_record(const V (&x)[1 << RB], int w, V *lds, const ObsDev *obs, int n_obs, double *out)
+{
+    constexpr int NT = 1 << (N - RB), WAVES = NT > 64 ? NT / 64 : 1;
+    __shared__ double red[WAVES][kMaxObs];
+    const uint32_t t0 = thread_part<RB>(threadIdx.x, w);
+    bool flips = false;
+    for (int o = 0; o < n_obs; ++o) flips = flips || obs[o].kind == 1 || obs[o].kind == 2;
+    resident_barrier<NT>();
+    if (flips) {
+#pragma unroll
+        for (int r = 0; r < (1 << RB); ++r) lds[lds_pos(t0 | ((uint32_t)r << w))] = x[r];
+        resident_barrier<NT>();
+    }
+    for (int o = 0; o < n_obs; ++o) {
+        const ObsDev ob = obs[o];
+        double acc = 0.0;
+        if (ob.kind == 1 || ob.kind == 2) {
+#pragma unroll
+            for (int r = 0; r < (1 << RB); ++r) {
+                const uint32_t t = t0 | ((uint32_t)r << w);
+                if ((t >> ob.i) & 1) continue;
+                const V u = lds[lds_pos(t | (1u << ob.i))];
+                const double cr = x[r].x, ci = x[r].y;
+                const double zr = cr * u.x + ci * u.y, zi = cr * u.y - ci * u.x;
+                acc += (ob.kind == 1) ? zr : -zi;
+            }
+        } else {
+#pragma unroll
+            for (int r = 0; r < (1 << RB); ++r) {
+                const uint32_t t = t0 | ((uint32_t)r << w);
+                const double cr = x[r].x, ci = x[r].y, p = cr * cr + ci * ci;
+                double f = 1.0;
+                if (ob.kind == 3) f = ((t >> ob.i) & 1) ? 0.5 : -0.5;
+                if (ob.kind == 4) f = (((t >> ob.i) ^ (t >> ob.j)) & 1) ? -0.25 : 0.25;
+                if (ob.kind == 5) f = (double)__popc(t) - 0.5 * N;
+                acc += f * p;
+            }
+        }
+#pragma unroll
+        for (int off = (NT > 64 ? 64 : NT) / 2; off > 0; off >>= 1) acc += __shfl_down(acc, off, 64);
+        if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][o] = acc;
+    }
+    resident_barrier<NT>();
+    for (int o = threadIdx.x; o < n_obs; o += NT) {
+        double s = 0.0;
+        for (int k = 0; k < WAVES; ++k) s += red[k][o];
+        out[obs[o].slot] = s;
+    }
+    resident_barrier<NT>();
+}
+
+// FAC: one system, alone on its CU: the phase steps multiply by factors formed once per plan,
+// loaded one op ahead, and the exchange buffer is double.  Otherwise (many chains) several
+// workgroups share a CU: the factors are formed from the small tables (a chain's factors
+// would take 64 KB per phase step at N = 12, more than the caches hold for 256 chains).
+template <typename R, int N, bool SOLO>
+__global__ __launch_bounds__(resident_threads(N)) void resident_kernel(ResidentArgs a)
+{
+    constexpr bool FAC = SOLO && N <= kResidentFactorSpins, FACL = FAC && N <= kResidentFactorLdsSpins;
     using V = typename Vec<R>::T;
-    constexpr int NV = T - kFixedBits;
-    __shared__ V tile[1 << T];
-    __shared__ double2 qtab[1 << NV];
+    constexpr int RB = resident_reg_bits(N), NT = 1 << (N - RB), E = 1 << RB;
+    constexpr int NW = (N + RB - 1) / RB, WT = N - RB;   // windows; start of the highest one
+    constexpr bool ASC = resident_ascending(std::is_same<R, float>::value);
+    constexpr int HALF = (1 << N) + ((1 << N) >> 4) + 1;
+    constexpr int B2 = SOLO && 2 * HALF * sizeof(V) <= 140 * 1024 ? HALF : 0;
+    __shared__ V buf[HALF + B2];
+    ResidentLds<V, B2> lds{buf, false};
+    const uint32_t tid = threadIdx.x;
     V *psi;
-    const double *wg[3], *jt[3];
+    const double *tab = a.tab;
     double *rec = nullptr;
     if (a.chains) {  // batched: one chain per workgroup
-        const ResidentChain ch = a.chains[blockIdx.x];
-        psi = static_cast<V *>(ch.psi);
-        for (int x = 0; x < 3; ++x) {
-            wg[x] = ch.wg[x];
-            jt[x] = ch.jt[x];
-        }
-        rec = ch.rec;
+        psi = static_cast<V *>(a.chains[blockIdx.x].psi);
+        rec = a.chains[blockIdx.x].rec;
+        tab += 2 * (size_t)blockIdx.x * a.n_phases * resident_phase_entries(N);
     } else {
         psi = reinterpret_cast<V *>(a.psi[blockIdx.x]);
-        for (int x = 0; x < 3; ++x) {
-            wg[x] = a.wg[x];
-            jt[x] = a.jt[x];
-        }
     }
-    const int ne = 1 << a.n;
-    for (int t = threadIdx.x; t < ne; t += kThreads) tile[t] = psi[t];
-    __syncthreads();
-    const uint32_t all = (uint32_t)(ne - 1);
+    V x[E];
+#pragma unroll
+    for (int r = 0; r < E; ++r) x[r] = psi[tid + r * NT];
     const int reps = a.n_rep > 0 ? a.n_rep : 1;
+    bool top = true;   // the register window: the highest or the lowest
+    // the next phase step's factors, or the thread's row of its table, loaded one op ahead
+    extern __shared__ double2 resident_dyn[];
+    if constexpr (FACL) {
+        const double2 *f = reinterpret_cast<const double2 *>(a.fac);
+        for (int i = tid; i < a.n_phases << N; i += NT) resident_dyn[i] = f[i];   // each thread reads what it wrote
+    }
+    double2 th[FAC ? E : 1 + RB];
+    auto load_row = [&](int phase) {
+        const double2 *t = FACL  ? resident_dyn + ((size_t)phase << N)
+                           : FAC ? reinterpret_cast<const double2 *>(a.fac) + ((size_t)phase << N)
+                                 : reinterpret_cast<const double2 *>(tab) + (size_t)phase * resident_phase_entries(N);
+#pragma unroll
+        for (int v = 0; v < (FAC ? E : 1 + RB); ++v) th[v] = t[v * NT + tid];
+    };
+    // the ops are read with scalar loads, two ahead
+    typedef const __attribute__((address_space(4))) ResidentOp *cop;
+    const cop ops = (cop)(const __attribute__((address_space(4))) void *)a.ops;
+    auto op_at = [&](int s) {
+        while (s >= a.n_ops) s -= a.n_ops;
+        const cop o = ops + s;
+        return ResidentOp{o->phase, o->post, o->rec, o->start};
+    };
+    ResidentOp op1{-1, 0, -1, 0}, op2 = op1;
+    if (a.n_ops > 0) {
+        op1 = op_at(0);
+        op2 = op_at(1);
+    }
+    load_row(op1.phase >= 0 ? op1.phase : 0);
+    if (a.rec_first) resident_record<N, RB>(x, WT, buf, a.obs, a.n_obs, a.rec_rows - a.slots);
     for (int r = 0; r < reps; ++r) {
         for (int s = 0; s < a.n_ops; ++s) {
-            const ResidentOp op = a.ops[s];
-            if (op.fac) {
-                for (int t = threadIdx.x; t < ne; t += kThreads) apply_phase(tile[t], op.fac[t]);
-                __syncthreads();
-            } else if (op.d.axis >= 0) {
-                const int ax = op.d.axis < 3 ? op.d.axis : 0;
-                build_qtab<T>(qtab, op.d, jt[ax]);
-                __syncthreads();
-                diag_step<T>(tile, ne, op.d, wg[ax], jt[ax], qtab, (uint64_t)threadIdx.x);
-                __syncthreads();
+            const ResidentOp op = op1;
+            op1 = op2;
+            op2 = op_at(s + 2);
+            if constexpr (NW > 1 && !ASC) {
+                if (op.start && !top) {  // every segment starts alike: the same arithmetic
+                    resident_transpose<NT, RB, 0, WT>(x, lds);
+                    top = true;
+                }
             }
-            if (op.post) wht_layer(tile, ne, all);
-            if (op.rec >= 0 && rec) resident_record(tile, ne, a.n, a.obs, a.n_obs, rec + (size_t)op.rec * a.slots);
+            if (op.phase >= 0) {
+                if constexpr (FAC) {
+#pragma unroll
+                    for (int j = 0; j < E; ++j) apply_phase(x[j], th[j]);
+                } else {
+                    const ctab q = as_const(tab) +
+                                   2 * ((size_t)op.phase * resident_phase_entries(N) + NT * (1 + RB));
+                    resident_phase<RB, RB>(th[0], 0, th, q, [&](int j, double2 z) { apply_phase(x[j], z); });
+                }
+            }
+            if (op1.phase >= 0) load_row(op1.phase);
+            if (op.post) {
+                if constexpr (NW == 1) {
+                    resident_layer<N, RB, 0, false>(x, lds);
+                } else if constexpr (ASC) {
+                    resident_transpose<NT, RB, WT, 0>(x, lds);
+                    resident_layer<N, RB, 0, false>(x, lds);
+                } else {
+                    if (top)
+                        resident_layer<N, RB, NW - 1, true>(x, lds);
+                    else
+                        resident_layer<N, RB, 0, false>(x, lds);
+                    top = !top;
+                }
+            }
+            if (op.rec >= 0 && rec)
+                resident_record<N, RB>(x, top ? WT : 0, buf, a.obs, a.n_obs, rec + (size_t)op.rec * a.slots);
         }
-        if (a.rec_rows) resident_record(tile, ne, a.n, a.obs, a.n_obs, a.rec_rows + (size_t)r * a.slots);
+        if (a.rec_rows)
+            resident_record<N, RB>(x, top ? WT : 0, buf, a.obs, a.n_obs, a.rec_rows + (size_t)r * a.slots);
     }
-    for (int t = threadIdx.x; t < ne; t += kThreads) psi[t] = tile[t];
-}
-
-// Phase factors of the resident ops, one workgroup per op: the op's phase step applied to a
-// tile of ones leaves in each entry exactly the factor that the step multiplies that
-// amplitude by (the product with 1 + 0i is exact), so applying the stored factors gives
-// the same amplitudes as forming them in the resident kernel.
-template <int T>
-__global__ __launch_bounds__(kThreads) void resident_factor_kernel(ResidentArgs a, double2 *out)
-{
-    constexpr int NV = T - kFixedBits;
-    __shared__ double2 tile[1 << T];
-    __shared__ double2 qtab[1 << NV];
-    const ResidentOp op = a.ops[blockIdx.x];
-    if (op.d.axis < 0) return;
-    const int ne = 1 << a.n;
-    for (int t = threadIdx.x; t < ne; t += kThreads) tile[t] = make_double2(1.0, 0.0);
-    const int ax = op.d.axis < 3 ? op.d.axis : 0;
-    build_qtab<T>(qtab, op.d, a.jt[ax]);
-    __syncthreads();
-    diag_step<T>(tile, ne, op.d, a.wg[ax], a.jt[ax], qtab, (uint64_t)threadIdx.x);
-    __syncthreads();
-    double2 *o = out + ((size_t)blockIdx.x << a.n);
-    for (int t = threadIdx.x; t < ne; t += kThreads) o[t] = tile[t];
+    if constexpr (NW > 1 && !ASC) {
+        if (!top) resident_transpose<NT, RB, 0, WT>(x, lds);
+    }
+#pragma unroll
+    for (int r = 0; r < E; ++r) psi[tid + r * NT] = x[r];
 }
 
 // ----------------------------------------------------------------------- reductions
@@ -2537,18 +2731,31 @@ hipError_t launch_sweep_reg_batch(int dtype, int T, int RB, const RegSweepArgs &
     return launch_reg_any(dtype, T, RB, nullptr, a, (uint64_t)nchains * a.tiles_per_chain, s);
 }
 
-template <typename R, int T>
-static hipError_t launch_res_t(const ResidentArgs &a, int nvec, hipStream_t s)
+template <typename R, int N>
+static hipError_t launch_res_n(const ResidentArgs &a, int nvec, hipStream_t s)
 {
-    hipLaunchKernelGGL((resident_kernel<R, T>), dim3(nvec), dim3(kThreads), 0, s, a);
+    const size_t dyn = N <= kResidentFactorLdsSpins ? ((size_t)a.n_phases << N) * sizeof(double2) : 0;
+    if (!a.chains && (a.fac || N > kResidentFactorSpins) && dyn <= 48 * 1024) {
+        hipLaunchKernelGGL((resident_kernel<R, N, true>), dim3(nvec), dim3(resident_threads(N)), dyn, s, a);
+        return hipGetLastError();
+    }
+    hipLaunchKernelGGL((resident_kernel<R, N, false>), dim3(nvec), dim3(resident_threads(N)), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_resident(int dtype, int T, const ResidentArgs &a, int nvec, hipStream_t s)
+hipError_t launch_resident(int dtype, const ResidentArgs &a, int nvec, hipStream_t s)
 {
-#define TS_RES_CASE(TT) \
-    case TT: return dtype == 0 ? launch_res_t<double, TT>(a, nvec, s) : launch_res_t<float, TT>(a, nvec, s);
-    switch (T) {
+    if (!a.tab || a.n_ops < 0 || nvec <= 0 || (a.chains && a.fac)) return hipErrorInvalidValue;
+#define TS_RES_CASE(NN) \
+    case NN: return dtype == 0 ? launch_res_n<double, NN>(a, nvec, s) : launch_res_n<float, NN>(a, nvec, s);
+    switch (a.n) {
+        TS_RES_CASE(1)
+        TS_RES_CASE(2)
+        TS_RES_CASE(3)
+        TS_RES_CASE(4)
+        TS_RES_CASE(5)
+        TS_RES_CASE(6)
+        TS_RES_CASE(7)
         TS_RES_CASE(8)
         TS_RES_CASE(9)
         TS_RES_CASE(10)
@@ -2556,7 +2763,7 @@ hipError_t launch_resident(int dtype, int T, const ResidentArgs &a, int nvec, hi
         TS_RES_CASE(12)
         TS_RES_CASE(13)
     case 14:
-        if (dtype == 1) return launch_res_t<float, 14>(a, nvec, s);
+        if (dtype == 1) return launch_res_n<float, 14>(a, nvec, s);
         break;
     default: break;
     }
@@ -2564,21 +2771,35 @@ hipError_t launch_resident(int dtype, int T, const ResidentArgs &a, int nvec, hi
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_resident_factors(int T, const ResidentArgs &a, double2 *out, hipStream_t s)
+hipError_t launch_resident_phases(const ResidentPhaseArgs &a, int nchains, hipStream_t s)
 {
-    if (a.chains || a.n_ops <= 0 || a.n > T) return hipErrorInvalidValue;
-#define TS_RESF_CASE(TT)                                                                                 \
-    case TT:                                                                                             \
-        hipLaunchKernelGGL((resident_factor_kernel<TT>), dim3((uint32_t)a.n_ops), dim3(kThreads), 0, s, a, \
-                           out);                                                                         \
+    if (a.n < 1 || a.n > 14 || a.n_phases <= 0 || !a.phases || !a.tab || (nchains > 0) != (a.chains != nullptr))
+        return hipErrorInvalidValue;
+    const int nt = resident_threads(a.n) > 16 ? resident_threads(a.n) : 16;
+    hipLaunchKernelGGL(resident_phase_kernel, dim3(a.n_phases, nchains > 0 ? nchains : 1), dim3(nt), 0, s, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_resident_factors(int n, int n_phases, const double *tab, double *fac, hipStream_t s)
+{
+    if (n_phases <= 0 || !tab || !fac) return hipErrorInvalidValue;
+#define TS_RESF_CASE(NN)                                                                              \
+    case NN:                                                                                          \
+        hipLaunchKernelGGL((resident_factor_kernel<NN>), dim3(n_phases), dim3(resident_threads(NN)), 0, s, tab, fac); \
         return hipGetLastError();
-    switch (T) {
+    switch (n) {
+        TS_RESF_CASE(1)
+        TS_RESF_CASE(2)
+        TS_RESF_CASE(3)
+        TS_RESF_CASE(4)
+        TS_RESF_CASE(5)
+        TS_RESF_CASE(6)
+        TS_RESF_CASE(7)
         TS_RESF_CASE(8)
         TS_RESF_CASE(9)
         TS_RESF_CASE(10)
         TS_RESF_CASE(11)
         TS_RESF_CASE(12)
-        TS_RESF_CASE(13)
     default: break;
     }
 #undef TS_RESF_CASE

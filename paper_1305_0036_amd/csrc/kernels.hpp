@@ -156,14 +156,37 @@ struct ConeArgs {
     ConePhaseArgs ph[kConePhases];
 };
 
+// One op of a state that fits one workgroup: phase step `phase` (index into the plan's phase
+// tables, -1: none), then the butterflies on every bit (post), then a record.
 struct ResidentOp {
-    DiagArgs d;
-    int32_t post;       // 1: butterflies on every bit after the phase step
+    int32_t phase;
+    int32_t post;
     int32_t rec;        // >= 0: record the observables as record `rec` after this op
-    // non-NULL: the phase step's factor of every amplitude (2^n, from
-    // launch_resident_factors), applied instead of forming it
-    const double2 *fac;
+    int32_t start;      // 1: a segment starts here, in the highest register window
 };
+
+// A distinct phase step of a resident plan and the register window it runs in (the highest
+// or the lowest of the kernel's windows: ops alternate between the two).
+struct ResidentPhase {
+    DiagArgs d;
+    int32_t top, pad;
+};
+
+// log2 of the amplitudes per thread and the number of threads of the resident kernel for n spins.
+__host__ __device__ constexpr int resident_reg_bits(int n) { return n <= 3 ? n : n <= 12 ? 3 : 4; }
+__host__ __device__ constexpr int resident_threads(int n) { return 1 << (n - resident_reg_bits(n)); }
+// (re, im) entries of one phase table: per thread [1 + RB] (entry-major), then [2^RB].
+__host__ __device__ constexpr int resident_phase_entries(int n)
+{
+    return resident_threads(n) * (1 + resident_reg_bits(n)) + (1 << resident_reg_bits(n));
+}
+// Most spins for which the kernel holds a phase step's factors ahead (at 13, with twice the
+// amplitudes per thread, they would spill), and for which it keeps all of them in LDS.
+constexpr int kResidentFactorSpins = 12;
+constexpr int kResidentFactorLdsSpins = 8;
+// complex64 keeps one order of a layer's butterflies (bits ascending): its layers all start in
+// the lowest window and every phase step runs in the highest.
+__host__ __device__ constexpr bool resident_ascending(int dtype) { return dtype == 1; }
 
 struct ObsDev {
     int32_t kind, i, j, ket, bra, slot;
@@ -197,16 +220,34 @@ struct ResidentArgs {
     void *psi[kMaxVec];
     const ResidentOp *ops;
     int32_t n_ops;
-    int32_t n;            // spins (<= T)
-    const double *wg[3];  // per axis [T+1]: 0, then the field on each bit (NULL: axis unused)
-    const double *jt[3];  // per axis [T][T]
-    const ResidentChain *chains;  // batched: per-workgroup state, tables and records
+    int32_t n;            // spins
+    // phase tables [n_phases][resident_phase_entries(n)] of (re, im) pairs, from
+    // launch_resident_phases; batched: chain c's tables start at phase c * n_phases
+    const double *tab;
+    // non-NULL (not batched): every phase step's factors [n_phases][2^n] (register-major, as the
+    // threads hold the amplitudes), from launch_resident_factors
+    const double *fac;
+    const ResidentChain *chains;  // batched: per-workgroup state, energies and records
+    int32_t n_phases;
     ObsDev obs[kMaxObs];          // observables of the record ops (real kinds)
     int32_t n_obs, slots;
     // One vector only: run the op list n_rep times (0 counts as 1) and, when rec_rows is
-    // set, record the observables into rec_rows[r * slots ...] after repetition r.
-    int32_t n_rep;
+    // set, record the observables into rec_rows[r * slots ...] after repetition r, and
+    // (rec_first) into the row before rec_rows before the first.
+    int32_t n_rep, rec_first;
     double *rec_rows;
+};
+
+// What the phase tables are built from: the energies of one system (or of every chain) per
+// axis, [T+1] = 0, then the field on each bit, and [T][T] couplings (upper triangle; NULL:
+// axis unused), T = max(n, 8).
+struct ResidentPhaseArgs {
+    const ResidentPhase *phases;
+    int32_t n_phases, n;
+    const double *wg[3];
+    const double *jt[3];
+    const ResidentChain *chains;
+    double *tab;
 };
 
 // Batched FP64 observables of many chains of one size (real kinds only).
@@ -368,10 +409,11 @@ hipError_t launch_cone_batch(int dtype, int T, int RB, void *packed, const int64
 hipError_t launch_sweep(int dtype, int T, void *psi, const SweepArgs &a, uint32_t nblocks,
                         hipStream_t s);
 hipError_t launch_sweep_reg(int dtype, int T, int RB, void *psi, const RegSweepArgs &a, hipStream_t s);
-hipError_t launch_resident(int dtype, int T, const ResidentArgs &a, int nvec, hipStream_t s);
-// The phase factors of a's ops (one vector's tables; every op with a phase step): op k's
-// factor of amplitude t to out[k * 2^n + t].  T <= 13.
-hipError_t launch_resident_factors(int T, const ResidentArgs &a, double2 *out, hipStream_t s);
+hipError_t launch_resident(int dtype, const ResidentArgs &a, int nvec, hipStream_t s);
+// Fills the phase tables of one system (nchains = 0) or of every chain.
+hipError_t launch_resident_phases(const ResidentPhaseArgs &a, int nchains, hipStream_t s);
+// The factors of one system's phase tables `tab`.
+hipError_t launch_resident_factors(int n, int n_phases, const double *tab, double *fac, hipStream_t s);
 hipError_t launch_reduce(int dtype, const ReduceArgs &a, double *partials, int nblocks,
                          double *out, hipStream_t s);
 

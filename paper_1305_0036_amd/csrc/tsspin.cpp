@@ -74,10 +74,10 @@ struct EnergyTable {
 
 struct PlanEntry {
     ts::Plan plan;
-    DevBuf resident_ops;   // ResidentOp[] when plan.resident
-    // one vector's resident ops with precomputed phase factors (N <= 13): the factors of the
-    // distinct phase steps, those steps' ops, and the op list that points at the factors
-    DevBuf resident_fac, resident_uniq, resident_fac_ops;
+    // when plan.resident: ResidentOp[], the distinct phase steps ResidentPhase[], their tables
+    // and factors
+    DevBuf resident_ops, resident_phases, resident_tab, resident_fac;
+    int resident_n_ops = 0, resident_n_phases = 0;
     std::vector<tsk::DiagArgs> diag_args;  // one per chain diagonal
     bool prepared = false;                 // launch arguments below are built
     int reg_bits = 0;
@@ -144,7 +144,6 @@ struct ts_ctx {
     DevBuf cone_partials;  // observables folded into light-cone sweeps: [workgroups][2 * kMaxObs]
     int64_t cone_partial_rows = 0;   // workgroups of the last sweep that wrote them
     bool no_fuse = false;  // $TSSPIN_NO_FUSE: records always by separate reductions
-    bool res_fac = true;   // $TSSPIN_RESIDENT_FACTORS=0: resident ops form their phases in place
     bool adj_split = false;  // $TSSPIN_ADJ_SPLIT: the adjoint's split-phase plan and separate gradient passes
     bool adj_cone = true;    // $TSSPIN_ADJ_CONE=0: the adjoint's reverse pass keeps the ping-pong form
     DevBuf expect_out;     // ts_expect staging
@@ -446,23 +445,35 @@ ts_status resolve_tile(ts_ctx *c, int dtype, int order, double dt, int64_t nstep
     return TS_OK;
 }
 
-// Upload the resident op list (needs the device).
-ts_status resident_ops(PlanEntry *pe)
+// Append a resident plan's ops to `ops`, and its phase steps to `phases` where they are not
+// there yet.  A phase step's table is for one of the kernel's two end windows: the plan
+// starts in the highest one and every layer changes to the other (where it alternates).
+void resident_append(const PlanEntry *pe, int dtype, std::vector<tsk::ResidentOp> &ops,
+                     std::vector<tsk::ResidentPhase> &phases)
 {
-    if (pe->resident_ops.p) return TS_OK;
-    std::vector<tsk::ResidentOp> ops;
+    const bool one = pe->plan.n <= tsk::resident_reg_bits(pe->plan.n) || tsk::resident_ascending(dtype);
+    bool top = true, first = true;
     for (const auto &s : pe->plan.sweeps) {
-        tsk::ResidentOp op{};
-        op.d = s.diag >= 0 ? pe->diag_args[s.diag] : tsk::DiagArgs{-1, 0, 0.0, 1.0, 0.0};
-        op.post = s.post_mask != 0;
-        op.rec = -1;
+        tsk::ResidentOp op{-1, s.post_mask != 0, -1, first};
+        first = false;
+        if (s.diag >= 0 && pe->diag_args[s.diag].axis >= 0) {
+            const tsk::DiagArgs &d = pe->diag_args[s.diag];
+            for (size_t u = 0; u < phases.size() && op.phase < 0; ++u) {
+                const tsk::DiagArgs &e = phases[u].d;
+                if (phases[u].top == top && e.axis == d.axis && e.qturn == d.qturn && e.tau == d.tau &&
+                    e.kre == d.kre && e.kim == d.kim)
+                    op.phase = (int)u;
+            }
+            if (op.phase < 0) {
+                op.phase = (int)phases.size();
+                phases.push_back(tsk::ResidentPhase{d, top, 0});
+            }
+        }
+        if (op.post && !one) top = !top;
         ops.push_back(op);
     }
-    ts_status st = alloc(pe->resident_ops, ops.size() * sizeof(tsk::ResidentOp));
-    if (st != TS_OK) return st;
-    TS_HIP(hipMemcpy(pe->resident_ops.p, ops.data(), ops.size() * sizeof(tsk::ResidentOp),
-                     hipMemcpyHostToDevice));
-    return TS_OK;
+    // the kernel's first table row is loaded whether an op uses it or not
+    if (phases.empty()) phases.push_back(tsk::ResidentPhase{tsk::DiagArgs{3, 0, 0.0, 1.0, 0.0}, 1, 0});
 }
 
 bool fill_runs(uint64_t mask, tsk::Run *runs, int32_t *nruns)
@@ -1354,91 +1365,68 @@ ts_status run_sweep(ts_ctx *c, PlanEntry *pe, size_t k, int dtype, void *const *
     return TS_OK;
 }
 
-// A plan repeats a few phase steps (the same axis, step, scalar and quarter turns) many
-// times: their factors per amplitude are formed once per plan (one workgroup each) and the
-// resident kernel then multiplies by them, with the same rounding as forming them in place.
-// Only for states of at most 2^13 amplitudes (the factor kernel's tile is complex128).
-ts_status resident_factors(ts_ctx *c, PlanEntry *pe, tsk::ResidentArgs *ra)
+// Op list and phase tables of a resident plan (one system: every bit is in the tile, so the
+// workgroup energies are the fields).
+ts_status resident_args(ts_ctx *c, PlanEntry *pe, int dtype, tsk::ResidentArgs *ra)
 {
-    const int n = c->n;
-    if (n > 13 || !c->res_fac) return TS_OK;
-    if (!pe->resident_fac_ops.p) {
-        std::vector<tsk::ResidentOp> ops, uniq;
-        std::vector<int> which;
-        for (const auto &sw : pe->plan.sweeps) {
-            tsk::ResidentOp op{};
-            op.d = sw.diag >= 0 ? pe->diag_args[sw.diag] : tsk::DiagArgs{-1, 0, 0.0, 1.0, 0.0};
-            op.post = sw.post_mask != 0;
-            op.rec = -1;
-            int k = -1;
-            if (op.d.axis >= 0) {
-                for (size_t u = 0; u < uniq.size() && k < 0; ++u) {
-                    const tsk::DiagArgs &e = uniq[u].d;
-                    if (e.axis == op.d.axis && e.qturn == op.d.qturn && e.tau == op.d.tau &&
-                        e.kre == op.d.kre && e.kim == op.d.kim)
-                        k = (int)u;
-                }
-                if (k < 0) {
-                    k = (int)uniq.size();
-                    uniq.push_back(op);
-                }
-            }
-            ops.push_back(op);
-            which.push_back(k);
+    const int n = c->n, Tk = n < 8 ? 8 : n;
+    if (!pe->resident_tab.p) {
+        std::vector<tsk::ResidentOp> ops;
+        std::vector<tsk::ResidentPhase> phases;
+        resident_append(pe, dtype, ops, phases);
+        tsk::ResidentPhaseArgs pa{};
+        for (int a = 0; a < 3; ++a) {
+            if (c->zero_axis[a]) continue;
+            EnergyTable *t;
+            ts_status st = get_table(c, Tk, (1ull << n) - 1, a, &t);
+            if (st != TS_OK) return st;
+            pa.wg[a] = static_cast<const double *>(t->wg.p);
+            pa.jt[a] = static_cast<const double *>(t->jt.p);
         }
-        if (uniq.empty()) return TS_OK;
-        const size_t ne = (size_t)1 << n;
-        ts_status st = alloc(pe->resident_fac, uniq.size() * ne * sizeof(double2));
+        ts_status st = alloc(pe->resident_ops, std::max<size_t>(1, ops.size()) * sizeof(tsk::ResidentOp));
         if (st != TS_OK) return st;
-        st = alloc(pe->resident_uniq, uniq.size() * sizeof(tsk::ResidentOp));
+        st = alloc(pe->resident_phases, phases.size() * sizeof(tsk::ResidentPhase));
         if (st != TS_OK) return st;
-        TS_HIP(hipMemcpy(pe->resident_uniq.p, uniq.data(), uniq.size() * sizeof(tsk::ResidentOp),
+        DevBuf tab;
+        st = alloc(tab, phases.size() * tsk::resident_phase_entries(n) * sizeof(double2));
+        if (st != TS_OK) return st;
+        const bool fac = n <= tsk::kResidentFactorSpins;
+        if (fac) st = alloc(pe->resident_fac, (phases.size() << n) * sizeof(double2));
+        if (st != TS_OK) return st;
+        TS_HIP(hipMemcpy(pe->resident_ops.p, ops.data(), ops.size() * sizeof(tsk::ResidentOp),
                          hipMemcpyHostToDevice));
-        tsk::ResidentArgs fa = *ra;
-        fa.ops = static_cast<const tsk::ResidentOp *>(pe->resident_uniq.p);
-        fa.n_ops = (int)uniq.size();
-        double2 *fac = static_cast<double2 *>(pe->resident_fac.p);
-        TS_HIP(tsk::launch_resident_factors(n < 8 ? 8 : n, fa, fac, nullptr));
-        for (size_t i = 0; i < ops.size(); ++i)
-            if (which[i] >= 0) ops[i].fac = fac + (size_t)which[i] * ne;
-        st = alloc(pe->resident_fac_ops, ops.size() * sizeof(tsk::ResidentOp));
-        if (st != TS_OK) return st;
-        TS_HIP(hipMemcpy(pe->resident_fac_ops.p, ops.data(), ops.size() * sizeof(tsk::ResidentOp),
+        TS_HIP(hipMemcpy(pe->resident_phases.p, phases.data(), phases.size() * sizeof(tsk::ResidentPhase),
                          hipMemcpyHostToDevice));
+        pa.phases = static_cast<const tsk::ResidentPhase *>(pe->resident_phases.p);
+        pa.n_phases = (int)phases.size();
+        pa.n = n;
+        pa.tab = static_cast<double *>(tab.p);
+        TS_HIP(tsk::launch_resident_phases(pa, 0, nullptr));
+        if (fac) TS_HIP(tsk::launch_resident_factors(n, pa.n_phases, pa.tab, static_cast<double *>(pe->resident_fac.p), nullptr));
+        TS_HIP(hipStreamSynchronize(nullptr));  // the tables are read on any stream
+        pe->resident_n_ops = (int)ops.size();
+        pe->resident_n_phases = (int)phases.size();
+        std::swap(pe->resident_tab.p, tab.p);
+        std::swap(pe->resident_tab.bytes, tab.bytes);
     }
-    ra->ops = static_cast<const tsk::ResidentOp *>(pe->resident_fac_ops.p);
+    ra->ops = static_cast<const tsk::ResidentOp *>(pe->resident_ops.p);
+    ra->n_ops = pe->resident_n_ops;
+    ra->n = n;
+    ra->tab = static_cast<const double *>(pe->resident_tab.p);
+    ra->fac = static_cast<const double *>(pe->resident_fac.p);
+    ra->n_phases = pe->resident_n_phases;
     return TS_OK;
 }
 
-// Op list and energy tables of a resident plan (the state fits one tile: no outside bits,
-// the workgroup factors are the fields, the thread tables hold every coupling).
-ts_status resident_args(ts_ctx *c, PlanEntry *pe, tsk::ResidentArgs *ra)
-{
-    ts_status st = resident_ops(pe);
-    if (st != TS_OK) return st;
-    const int n = c->n, Tk = n < 8 ? 8 : n;
-    std::array<EnergyTable *, 3> tab{};
-    for (int a = 0; a < 3; ++a) {
-        if (c->zero_axis[a]) continue;
-        st = get_table(c, Tk, (1ull << n) - 1, a, &tab[a]);
-        if (st != TS_OK) return st;
-    }
-    ra->ops = static_cast<const tsk::ResidentOp *>(pe->resident_ops.p);
-    ra->n_ops = (int)pe->plan.sweeps.size();
-    ra->n = n;
-    for (int a = 0; a < 3; ++a) {
-        ra->wg[a] = tab[a] ? static_cast<const double *>(tab[a]->wg.p) : nullptr;
-        ra->jt[a] = tab[a] ? static_cast<const double *>(tab[a]->jt.p) : nullptr;
-    }
-    return resident_factors(c, pe, ra);
-}
+// Phase tables that a batch keeps for one class of resident chains.
+constexpr size_t kResidentTabBytes = (size_t)1 << 30;
 
 // Segments one recorded resident launch runs at most.
 constexpr int64_t kResidentReps = 4096;
 
 // A recorded evolution of one vector that fits one tile, as single launches: `nseg` segments
-// of one cached plan each, with the observables (real kinds) recorded from LDS into
-// rows[k * slots ...] after segment k.  Returns false in *ran (and does nothing) when the
+// of one cached plan each, with the observables (real kinds) recorded in the kernel: row 0
+// before the first segment, row k + 1 after segment k.  Returns false in *ran (and does nothing) when the
 // segment's plan is not resident.
 ts_status run_resident_records(ts_ctx *c, int dtype, int T, int order, double dt, int64_t seg,
                                int64_t nseg, void *psi, const std::vector<tsk::ObsDev> &obs, int slots,
@@ -1450,7 +1438,7 @@ ts_status run_resident_records(ts_ctx *c, int dtype, int T, int order, double dt
     if (st != TS_OK) return st;
     if (!pe->plan.resident) return TS_OK;
     tsk::ResidentArgs ra{};
-    st = resident_args(c, pe, &ra);
+    st = resident_args(c, pe, dtype, &ra);
     if (st != TS_OK) return st;
     ra.psi[0] = psi;
     for (size_t k = 0; k < obs.size(); ++k) ra.obs[k] = obs[k];
@@ -1458,8 +1446,9 @@ ts_status run_resident_records(ts_ctx *c, int dtype, int T, int order, double dt
     ra.slots = slots;
     for (int64_t k = 0; k < nseg; k += kResidentReps) {
         ra.n_rep = (int32_t)std::min(kResidentReps, nseg - k);
-        ra.rec_rows = rows + (size_t)k * slots;
-        TS_HIP(tsk::launch_resident(dtype, c->n < 8 ? 8 : c->n, ra, 1, s));
+        ra.rec_rows = rows + (size_t)(k + 1) * slots;
+        ra.rec_first = k == 0;
+        TS_HIP(tsk::launch_resident(dtype, ra, 1, s));
     }
     *ran = true;
     return TS_OK;
@@ -1475,10 +1464,10 @@ ts_status run_plan(ts_ctx *c, PlanEntry *pe, int dtype, void *const *psi, int n_
     const int n = c->n;
     if (P.resident) {
         tsk::ResidentArgs ra{};
-        ts_status st = resident_args(c, pe, &ra);
+        ts_status st = resident_args(c, pe, dtype, &ra);
         if (st != TS_OK) return st;
         for (int v = 0; v < n_psi; ++v) ra.psi[v] = psi[v];
-        TS_HIP(tsk::launch_resident(dtype, n < 8 ? 8 : n, ra, n_psi, stream));
+        TS_HIP(tsk::launch_resident(dtype, ra, n_psi, stream));
         return TS_OK;
     }
     if (pe->cone) {
@@ -1799,14 +1788,23 @@ bool valid_config(int dtype, int n, int T, int RB, int variant)
     return n >= 1;
 }
 
+// Drop a batch's captured programs.  Each runs its classes on streams of its own, so an event
+// on the caller's stream does not say that they are done with the graph, its streams and its
+// buffers: wait for the device first.
+void drop_programs(ts_ctx *c)
+{
+    if (!c->programs.empty()) (void)hipDeviceSynchronize();
+    c->programs.clear();
+    c->program_order.clear();
+}
+
 void apply_config(ts_ctx *c, int dtype, int T, int RB, int variant)
 {
     c->tile_bits[dtype] = T;
     c->reg_bits[dtype] = RB;
     c->sweep_variant[dtype] = variant;
     for (auto &ch : c->chains) apply_config(ch.get(), dtype, T, RB, variant);
-    c->programs.clear();
-    c->program_order.clear();
+    drop_programs(c);
 }
 
 // First use of a dtype: take the cached tuning for this GPU and size, if there is one.
@@ -1827,10 +1825,11 @@ void consult_tune_cache(ts_ctx *c, int dtype, int order)
 // One kernel launch of a batched evolution.
 struct BatchLaunch {
     int kind = 0;                 // 0 resident, 1 batched sweep, 2 batched observables,
-                                  // 3 batched light-cone sweep
+                                  // 3 batched light-cone sweep, 4 resident phase tables
     int T = 0, RB = 0;
     uint32_t count = 0;           // workgroups (resident) or chains
     tsk::ResidentArgs ra{};
+    tsk::ResidentPhaseArgs pa{};
     tsk::RegSweepArgs sa{};
     tsk::BatchReduceArgs ba{};
     double *partials = nullptr;
@@ -1886,7 +1885,8 @@ ts_status upload(BatchProgram *bp, const std::vector<Tv> &v, const Tv **out)
 hipError_t run_launch(int dtype, const BatchLaunch &L, hipStream_t s)
 {
     switch (L.kind) {
-    case 0: return tsk::launch_resident(dtype, L.T, L.ra, (int)L.count, s);
+    case 0: return tsk::launch_resident(dtype, L.ra, (int)L.count, s);
+    case 4: return tsk::launch_resident_phases(L.pa, (int)L.count, s);
     case 1: return tsk::launch_sweep_reg_batch(dtype, L.T, L.RB, L.sa, L.count, s);
     case 3:
         return tsk::launch_cone_batch(dtype, L.T, L.RB, L.cone_packed, L.cone_off, L.cone_args, L.count, L.tiles,
@@ -1935,31 +1935,18 @@ ts_status build_batch_program(ts_ctx *ctx, char *psi_packed, const int64_t *psi_
         auto chain_psi = [&](int m) { return psi_packed + psi_off[m] * esz; };
         auto chain_rec = [&](int m) { return rec ? rec_out + (size_t)m * nrec * slots : nullptr; };
         if (n <= Tdef) {
-            // LDS-resident: the whole evolution of every chain of the class in one launch
+            // resident: the whole evolution of every chain of the class in one launch
             const int Tk = n < 8 ? 8 : n;
             std::vector<tsk::ResidentOp> ops;
-            auto add_plan = [&](PlanEntry *pe) {
-                for (const auto &s : pe->plan.sweeps) {
-                    tsk::ResidentOp op{};
-                    op.d = s.diag >= 0 ? pe->diag_args[s.diag] : tsk::DiagArgs{-1, 0, 0.0, 1.0, 0.0};
-                    op.post = s.post_mask != 0;
-                    op.rec = -1;
-                    ops.push_back(op);
-                }
-            };
-            auto add_rec = [&](int r) {
-                tsk::ResidentOp op{};
-                op.d = tsk::DiagArgs{-1, 0, 0.0, 1.0, 0.0};
-                op.post = 0;
-                op.rec = r;
-                ops.push_back(op);
-            };
+            std::vector<tsk::ResidentPhase> phases;
+            auto add_rec = [&](int r) { ops.push_back(tsk::ResidentOp{-1, 0, r, 0}); };
             if (rec) add_rec(0);
             for (int64_t k = 0; k < nseg; ++k) {
-                add_plan(ps);
+                resident_append(ps, dtype, ops, phases);
                 if (rec) add_rec((int)(k + 1));
             }
-            if (pr) add_plan(pr);
+            if (pr) resident_append(pr, dtype, ops, phases);
+            if (phases.empty()) phases.push_back(tsk::ResidentPhase{tsk::DiagArgs{3, 0, 0.0, 1.0, 0.0}, 1, 0});
             std::vector<tsk::ResidentChain> rc;
             for (int m : mem) {
                 ts_ctx *cm = ctx->chains[m].get();
@@ -1976,20 +1963,44 @@ ts_status build_batch_program(ts_ctx *ctx, char *psi_packed, const int64_t *psi_
                 }
                 rc.push_back(x);
             }
-            BatchLaunch bl;
+            // The phase tables of a class of many chains outgrow its states (about 60 KB per
+            // chain at 10 spins, 250 KB at 12): at most kResidentTabBytes of them are kept.
+            // A class that fits has them filled once, here; a larger one runs in groups of
+            // chains that share the buffer, each filling it anew.
+            const size_t per_chain = phases.size() * tsk::resident_phase_entries(n) * sizeof(double2);
+            const size_t group = std::min<size_t>(mem.size(),
+                                                  std::min<size_t>(65535, std::max<size_t>(1, kResidentTabBytes / per_chain)));
+            auto tb = std::make_unique<DevBuf>();
+            st = alloc(*tb, group * per_chain);
+            if (st != TS_OK) return st;
+            BatchLaunch bl, fill;
             bl.kind = 0;
-            bl.T = Tk;
-            bl.count = (uint32_t)mem.size();
+            fill.kind = 4;
             st = upload(bp, ops, &bl.ra.ops);
             if (st != TS_OK) return st;
             st = upload(bp, rc, &bl.ra.chains);
             if (st != TS_OK) return st;
+            st = upload(bp, phases, &fill.pa.phases);
+            if (st != TS_OK) return st;
             bl.ra.n_ops = (int)ops.size();
-            bl.ra.n = n;
+            bl.ra.n = fill.pa.n = n;
+            bl.ra.n_phases = fill.pa.n_phases = (int)phases.size();
+            bl.ra.tab = fill.pa.tab = static_cast<double *>(tb->p);
             for (size_t o = 0; o < obs.size(); ++o) bl.ra.obs[o] = obs[o];
             bl.ra.n_obs = (int)obs.size();
             bl.ra.slots = slots;
-            L.push_back(bl);
+            bp->bufs.push_back(std::move(tb));
+            const tsk::ResidentChain *all = bl.ra.chains;
+            for (size_t g = 0; g < mem.size(); g += group) {
+                bl.ra.chains = fill.pa.chains = all + g;
+                bl.count = fill.count = (uint32_t)std::min(group, mem.size() - g);
+                if (group < mem.size())
+                    L.push_back(fill);
+                else
+                    TS_HIP(tsk::launch_resident_phases(fill.pa, (int)fill.count, nullptr));
+                L.push_back(bl);
+            }
+            TS_HIP(hipStreamSynchronize(nullptr));
             bp->per_class.push_back(std::move(L));
             continue;
         }
@@ -2222,7 +2233,6 @@ ts_status ts_create(int32_t n_spins, const ts_bond *bonds, int32_t n_bonds, cons
     if (const char *v = std::getenv("TSSPIN_CONE")) c->cone_mode = std::atoi(v);
     if (const char *v = std::getenv("TSSPIN_CONE_ADV")) c->cone_adv = std::atoi(v);
     if (const char *v = std::getenv("TSSPIN_NO_FUSE")) c->no_fuse = std::strcmp(v, "0") != 0;
-    if (const char *v = std::getenv("TSSPIN_RESIDENT_FACTORS")) c->res_fac = std::strcmp(v, "0") != 0;
     if (const char *v = std::getenv("TSSPIN_ADJ_SPLIT")) c->adj_split = std::strcmp(v, "0") != 0;
     if (const char *v = std::getenv("TSSPIN_ADJ_CONE")) c->adj_cone = std::strcmp(v, "0") != 0;
     c->h.assign(n_spins, {0.0, 0.0, 0.0});
@@ -2321,10 +2331,6 @@ ts_status ts_evolve(ts_ctx *ctx, void *const *psi, int32_t n_psi, ts_dtype dtype
         st = reduce(ctx, dtype, cpsi, n_psi, norms, static_cast<double *>(ctx->watch_buf.p), s);
         if (st != TS_OK) return st;
     }
-    if (n_rec > 0) {
-        st = reduce(ctx, dtype, cpsi, n_psi, obs, rec_out, s);
-        if (st != TS_OK) return st;
-    }
     // Observables that need only the amplitude at b (and a bra evolved before the ket) are
     // accumulated by the last light-cone sweep of their ket vector, when the segment runs in
     // that form; the rest (spin flips: S^x, S^y, the energy) by a reduction afterwards.
@@ -2344,10 +2350,13 @@ ts_status ts_evolve(ts_ctx *ctx, void *const *psi, int32_t n_psi, ts_dtype dtype
     for (const tsk::ObsDev &o : obs) real_kinds = real_kinds && o.kind <= TS_OBS_MZ;
     if (n_rec > 0 && n_psi == 1 && nseg > 0 && seg <= kChunkSteps && real_kinds && !ctx->no_fuse) {
         bool ran = false;
-        st = run_resident_records(ctx, dtype, T, order, dt, seg, nseg, psi[0], obs, slots, rec_out + slots, s,
-                                  &ran);
+        st = run_resident_records(ctx, dtype, T, order, dt, seg, nseg, psi[0], obs, slots, rec_out, s, &ran);
         if (st != TS_OK) return st;
         if (ran) first = nseg;
+    }
+    if (n_rec > 0 && first == 0) {
+        st = reduce(ctx, dtype, cpsi, n_psi, obs, rec_out, s);
+        if (st != TS_OK) return st;
     }
     for (int64_t k = first; k < nseg; ++k) {
         bool fused = false;
@@ -2982,8 +2991,7 @@ extern "C" ts_status ts_set_tile_bits(ts_ctx *ctx, ts_dtype dtype, int32_t tile_
         ch->tile_bits[dtype] = tile_bits;
         ch->user_config[dtype] = tile_bits != 0;
     }
-    ctx->programs.clear();
-    ctx->program_order.clear();
+    drop_programs(ctx);
     return TS_OK;
 }
 
