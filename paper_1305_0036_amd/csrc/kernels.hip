@@ -2094,116 +2094,106 @@ __device__ __forceinline__ double wave_sum(double v)
     return v;
 }
 
-// Share of <psi|H|psi> (H of Sec. 2, Eq. 1) owned by basis index b: the diagonal part
-// D_z(b)|c_b|^2, and for every pair of basis states that an x or y term connects, twice
-// the real part of its matrix element, counted at the member whose flipped bits are clear.
-// S^x flips a spin with amplitude 1/2, S^y with +i/2 from down to up (bit clear to set)
-// and -i/2 back, so for one spin q and c = c_b, u = c_{b + 2^q} (bit q of b clear):
-//   h^x <S^x_q> + h^y <S^y_q>  gathers  h^x Re(conj(c) u) - h^y Im(conj(c) u),
-// and for a bond (i, j) with both bits of b clear, A = Re(conj(c_00) c_11),
-// B = Re(conj(c_01) c_10):  J^x <S^x S^x> + J^y <S^y S^y>  gathers  (J^x (A + B) + J^y (B - A)) / 2.
-template <typename V>
-__device__ __noinline__ double energy_density(const V *__restrict__ ket, uint64_t b, int n,
-                                              const double *__restrict__ hf,
-                                              const HamBond *__restrict__ hb, int nb)
-{
-    const V c = ket[b];
-    const double cr = c.x, ci = c.y;
-    double dz = 0.0, off = 0.0;
-    for (int q = 0; q < n; ++q) {
-        const bool up = (b >> q) & 1;
-        dz += hf[3 * q + 2] * (up ? 0.5 : -0.5);
-        const double hx = hf[3 * q], hy = hf[3 * q + 1];
-        if (!up && (hx != 0.0 || hy != 0.0)) {
-            const V u = ket[b | (1ull << q)];
-            const double zr = cr * u.x + ci * u.y, zi = cr * u.y - ci * u.x;
-            off += hx * zr - hy * zi;
-        }
-    }
-    for (int k = 0; k < nb; ++k) {
-        const HamBond t = hb[k];
-        const uint64_t mi = 1ull << t.i, mj = 1ull << t.j;
-        dz += t.jz * ((((b >> t.i) ^ (b >> t.j)) & 1) ? -0.25 : 0.25);
-        if ((t.jx != 0.0 || t.jy != 0.0) && !(b & (mi | mj))) {
-            const V c11 = ket[b | mi | mj], c01 = ket[b | mi], c10 = ket[b | mj];
-            const double A = cr * c11.x + ci * c11.y;
-            const double B = (double)c01.x * c10.x + (double)c01.y * c10.y;
-            off += 0.5 * (t.jx * (A + B) + t.jy * (B - A));
-        }
-    }
-    return dz * (cr * cr + ci * ci) + off;
-}
-
-template <typename R>
+// Sums of up to NO observables.  Bound by the read of each state involved (2^27 complex128
+// amplitudes and their overlap: 1.49 -> 0.70 ms, 6.1 TB/s): a thread holds kRedElems amplitudes at a
+// time, loaded together, and reads a state again only where the next observable names another.
+constexpr int kRedElems = 4;
+template <typename R, int NO>
 __global__ __launch_bounds__(kThreads) void reduce_kernel(ReduceArgs a, double *partials)
 {
     using V = typename Vec<R>::T;
-    double acc[kMaxObs][2];
+    constexpr int U = kRedElems;
+    double acc[NO][2];
 #pragma unroll
-    for (int o = 0; o < kMaxObs; ++o) acc[o][0] = acc[o][1] = 0.0;
+    for (int o = 0; o < NO; ++o) acc[o][0] = acc[o][1] = 0.0;
+    // the observables are read from LDS where they are used: all of them held across the loop
+    // do not fit the scalar registers
+    __shared__ ObsDev obs[NO];
+    if (threadIdx.x < NO) obs[threadIdx.x] = a.obs[threadIdx.x];
+    __syncthreads();
     const uint64_t dim = 1ull << a.n;
-    const uint64_t stride = (uint64_t)gridDim.x * kThreads;
-    for (uint64_t b = (uint64_t)blockIdx.x * kThreads + threadIdx.x; b < dim; b += stride) {
+    for (uint64_t b0 = (uint64_t)blockIdx.x * (U * kThreads); b0 < dim; b0 += (uint64_t)gridDim.x * (U * kThreads)) {
+        const uint64_t b1 = b0 + threadIdx.x;
+        V c[U];
+        double pr[U];   // |c|^2
+        int cur = -1;
+        auto load = [&](V(&x)[U], int v) {
+            const V *p = reinterpret_cast<const V *>(a.psi[v]);
 #pragma unroll
-        for (int o = 0; o < kMaxObs; ++o) {
+            for (int u = 0; u < U; ++u) x[u] = b1 + u * kThreads < dim ? p[b1 + u * kThreads] : V{0, 0};
+        };
+#pragma unroll
+        for (int o = 0; o < NO; ++o) {
             if (o >= a.n_obs) continue;
-            const ObsDev ob = a.obs[o];
+            asm volatile("" ::: "memory");
+            const ObsDev ob{__builtin_amdgcn_readfirstlane(obs[o].kind), __builtin_amdgcn_readfirstlane(obs[o].i),
+                            __builtin_amdgcn_readfirstlane(obs[o].j), __builtin_amdgcn_readfirstlane(obs[o].ket),
+                            __builtin_amdgcn_readfirstlane(obs[o].bra), 0};
+            if (ob.kind == 6) continue;
             const V *ket = reinterpret_cast<const V *>(a.psi[ob.ket]);
-            const V c = ket[b];
-            const double cr = c.x, ci = c.y;
-            const double p = cr * cr + ci * ci;
-            switch (ob.kind) {
-            case 0: acc[o][0] += p; break;
-            case 3: acc[o][0] += (((b >> ob.i) & 1) ? 0.5 : -0.5) * p; break;
-            case 4:
-                acc[o][0] += ((((b >> ob.i) ^ (b >> ob.j)) & 1) ? -0.25 : 0.25) * p;
-                break;
-            case 5: acc[o][0] += ((double)__popcll(b) - 0.5 * a.n) * p; break;
-            case 1:
-            case 2:
-                if (!((b >> ob.i) & 1)) {
-                    const V u = ket[b | (1ull << ob.i)];
-                    // conj(c) * u
-                    const double zr = cr * u.x + ci * u.y, zi = cr * u.y - ci * u.x;
-                    acc[o][0] += (ob.kind == 1) ? zr : -zi;
+            if (ob.ket != cur) {
+                load(c, ob.ket);
+                cur = ob.ket;
+#pragma unroll
+                for (int u = 0; u < U; ++u) pr[u] = (double)c[u].x * c[u].x + (double)c[u].y * c[u].y;
+            }
+            if (obs_complex(ob.kind)) {
+                V w[U];
+                load(w, ob.bra);
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const double cr = c[u].x, ci = c[u].y;
+                    const double f = ob.kind == kObsOverlap ? 1.0 : ((b1 + u * kThreads) >> ob.i) & 1 ? 0.5 : -0.5;
+                    acc[o][0] += f * ((double)w[u].x * cr + (double)w[u].y * ci);
+                    acc[o][1] += f * ((double)w[u].x * ci - (double)w[u].y * cr);
                 }
-                break;
-            case 6: acc[o][0] += energy_density<V>(ket, b, a.n, a.ham_h, a.ham_b, a.ham_nb); break;
-            case kObsSxSx:
-            case kObsSySy: {
-                // pairs (b, b + 2^i + 2^j) and (b + 2^i, b + 2^j) at the member with both bits clear
-                const uint64_t mi = 1ull << ob.i, mj = 1ull << ob.j;
-                if (!(b & (mi | mj))) {
-                    const V c11 = ket[b | mi | mj], c01 = ket[b | mi], c10 = ket[b | mj];
-                    const double A = cr * c11.x + ci * c11.y;
-                    const double B = (double)c01.x * c10.x + (double)c01.y * c10.y;
-                    acc[o][0] += 0.5 * (ob.kind == kObsSxSx ? A + B : B - A);
+                continue;
+            }
+            const uint64_t mi = 1ull << ob.i, mj = 1ull << ob.j;
+            if (ob.kind == 1 || ob.kind == 2) {
+                // every partner is loaded before one is used (a masked load each waits for its own)
+                V w[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const uint64_t b = b1 + u * kThreads;
+                    w[u] = ket[b < dim ? b | mi : 0];
                 }
-                break;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const double cr = c[u].x, ci = c[u].y;
+                    const double z = ob.kind == 1 ? cr * w[u].x + ci * w[u].y : ci * w[u].x - cr * w[u].y;
+                    acc[o][0] += ((b1 + u * kThreads) & mi) || b1 + u * kThreads >= dim ? 0.0 : z;
+                }
+                continue;
             }
-            case kObsOverlap: {
-                const V *bra = reinterpret_cast<const V *>(a.psi[ob.bra]);
-                const V w = bra[b];
-                acc[o][0] += (double)w.x * cr + (double)w.y * ci;
-                acc[o][1] += (double)w.x * ci - (double)w.y * cr;
-                break;
-            }
-            case 7: {
-                const V *bra = reinterpret_cast<const V *>(a.psi[ob.bra]);
-                const V w = bra[b];
-                const double s = ((b >> ob.i) & 1) ? 0.5 : -0.5;
-                acc[o][0] += s * ((double)w.x * cr + (double)w.y * ci);
-                acc[o][1] += s * ((double)w.x * ci - (double)w.y * cr);
-                break;
-            }
-            default: break;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint64_t b = b1 + u * kThreads;
+                const double cr = c[u].x, ci = c[u].y, p = pr[u];
+                switch (ob.kind) {
+                case 0: acc[o][0] += p; break;
+                case 3: acc[o][0] += ((b & mi) ? 0.5 : -0.5) * p; break;
+                case 4: acc[o][0] += ((((b >> ob.i) ^ (b >> ob.j)) & 1) ? -0.25 : 0.25) * p; break;
+                case 5: acc[o][0] += ((double)__popcll(b) - 0.5 * a.n) * p; break;
+                case kObsSxSx:
+                case kObsSySy:
+                    // pairs (b, b + 2^i + 2^j) and (b + 2^i, b + 2^j) at the member with both bits clear
+                    if (b < dim && !(b & (mi | mj))) {
+                        const V c11 = ket[b | mi | mj], c01 = ket[b | mi], c10 = ket[b | mj];
+                        const double A = cr * c11.x + ci * c11.y;
+                        const double B = (double)c01.x * c10.x + (double)c01.y * c10.y;
+                        acc[o][0] += 0.5 * (ob.kind == kObsSxSx ? A + B : B - A);
+                    }
+                    break;
+                default: break;
+                }
             }
         }
     }
-    __shared__ double red[kThreads / 64][kMaxObs * 2];
+    __shared__ double red[kThreads / 64][NO * 2];
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
 #pragma unroll
-    for (int o = 0; o < kMaxObs; ++o) {
+    for (int o = 0; o < NO; ++o) {
         if (o >= a.n_obs) continue;
         const double s0 = wave_sum(acc[o][0]), s1 = wave_sum(acc[o][1]);
         if (lane == 0) {
@@ -2212,32 +2202,112 @@ __global__ __launch_bounds__(kThreads) void reduce_kernel(ReduceArgs a, double *
         }
     }
     __syncthreads();
-    if (threadIdx.x < 2 * a.n_obs) {
+    if (threadIdx.x < 2 * a.n_obs && a.obs[threadIdx.x >> 1].kind != 6) {
         double s = 0.0;
         for (int w = 0; w < kThreads / 64; ++w) s += red[w][threadIdx.x];
         partials[(size_t)blockIdx.x * (2 * kMaxObs) + threadIdx.x] = s;
     }
 }
 
-// Sum the per-block partials in a fixed order and write the requested slots: one wavefront
-// per slot, each lane a Neumaier-compensated strided sum, then a fixed shuffle tree.
-__global__ __launch_bounds__(kThreads) void finalize_kernel(const double *partials, int nblocks,
-                                                            ReduceArgs a, double *out)
+// One pass of the energy (EnergyPass).  Each op reads its tile from LDS once, so a pass costs
+// the read of the state or, with about ten ops, that of the tile from LDS; gathering the
+// flipped partners of every basis index from memory instead read the state 0.75 times per
+// bond, by lanes of which three quarters waited.  N = 24 chain, complex128: 2.3 -> 0.22 ms in three passes.  The
+// next tile's amplitudes are under way while the ops run.
+template <typename R, int TM>
+__global__ __launch_bounds__(kThreads) void energy_kernel(const typename Vec<R>::T *__restrict__ psi, EnergyPass a,
+                                                          int first, double *__restrict__ partials)
 {
-    const int lane = threadIdx.x & 63;
-    for (int s = threadIdx.x >> 6; s < 2 * a.n_obs; s += kThreads / 64) {
-        double acc = 0.0, comp = 0.0;
-        for (int b = lane; b < nblocks; b += 64) {
-            const double x = partials[(size_t)b * (2 * kMaxObs) + s];
-            const double t = acc + x;
-            comp += (fabs(acc) >= fabs(x)) ? (acc - t) + x : (x - t) + acc;
-            acc = t;
+    using V = typename Vec<R>::T;
+    constexpr int EPT = 1 << (TM - kFixedBits);
+    __shared__ V tile[(1 << TM) + (1 << (TM - 4)) + 1];
+    __shared__ double red[kThreads / 64];
+    const uint32_t tid = threadIdx.x, ne = 1u << a.T;
+    const uint64_t lpart = dep(tid, a.tile_runs, a.n_tile_runs);
+    typedef const __attribute__((address_space(4))) EnergyOp *cops;
+    const cops ops = (cops)(const __attribute__((address_space(4))) void *)a.ops;
+    auto at = [&](uint32_t t) { return tile[lds_pos(t)]; };
+    V x[EPT];
+    auto fetch = [&](uint64_t t) {
+        const V *p = psi + dep(t, a.out_runs, a.n_out_runs);
+#pragma unroll
+        for (int k = 0; k < EPT; ++k)
+            x[k] = tid + k * kThreads < ne ? (p + dep(k * kThreads, a.tile_runs, a.n_tile_runs))[lpart] : V{0, 0};
+    };
+    double acc = 0.0;
+    uint64_t t = blockIdx.x;
+    if (t < a.n_tiles) fetch(t);
+    for (; t < a.n_tiles; t += gridDim.x) {
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < EPT; ++k)
+            if (tid + k * kThreads < ne) tile[lds_pos(tid + k * kThreads)] = x[k];
+        __syncthreads();
+        if (t + gridDim.x < a.n_tiles) fetch(t + gridDim.x);
+        for (int k = 0; k < a.n_ops; ++k) {
+            const cops op = ops + k;
+            const int qa = op->a, qb = op->b;
+            const double w0 = op->w[0], w1 = op->w[1], w2 = op->w[2], w3 = op->w[3], cA = op->cA, cB = op->cB;
+            auto dot = [](V c, V u) { return (double)c.x * u.x + (double)c.y * u.y; };
+            auto crs = [](V c, V u) { return (double)c.x * u.y - (double)c.y * u.x; };
+            if (qb < 0) {
+                if (tid < ne / 2) {
+                    const V c = at(tid << 1), u = at((tid << 1) | 1);
+                    acc += w0 * dot(c, c) + w1 * dot(u, u) + op->hx[0] * dot(c, u) - op->hy[0] * crs(c, u);
+                }
+                continue;
+            }
+            const uint32_t ma = 1u << qa, mb = 1u << qb;
+            const int lo = qa < qb ? qa : qb, hi = qa < qb ? qb : qa;
+            auto quad = [&](uint32_t q) {
+                const uint32_t e = ins0(ins0(q, lo), hi);
+                const V c00 = at(e), c10 = at(e | ma), c01 = at(e | mb), c11 = at(e | ma | mb);
+                double v = w0 * dot(c00, c00) + w1 * dot(c10, c10) + w2 * dot(c01, c01) + w3 * dot(c11, c11);
+                v += cA * dot(c00, c11) + cB * dot(c10, c01);
+                if (op->flips) {
+                    v += op->hx[0] * (dot(c00, c10) + dot(c01, c11)) - op->hy[0] * (crs(c00, c10) + crs(c01, c11));
+                    v += op->hx[1] * (dot(c00, c01) + dot(c10, c11)) - op->hy[1] * (crs(c00, c01) + crs(c10, c11));
+                }
+                acc += v;
+            };
+            if (ne == 1u << TM) {
+#pragma unroll
+                for (int k2 = 0; k2 < EPT / 4; ++k2) quad(tid + k2 * kThreads);
+            } else {
+                for (uint32_t q = tid; q < ne / 4; q += kThreads) quad(q);
+            }
         }
-        const double tot = wave_sum(acc + comp);
-        const int o = s >> 1, part = s & 1;
-        const ObsDev ob = a.obs[o];
-        if (lane == 0 && (part == 0 || obs_complex(ob.kind))) out[ob.slot + part] = tot;
     }
+    acc = wave_sum(acc);
+    if ((tid & 63) == 0) red[tid >> 6] = acc;
+    __syncthreads();
+    if (tid == 0) {
+        double s = 0.0;
+        for (int w = 0; w < kThreads / 64; ++w) s += red[w];
+        double *o = partials + (size_t)blockIdx.x * (2 * kMaxObs);
+        *o = first ? s : *o + s;
+    }
+}
+
+// Sum the per-block partials in a fixed order and write the requested slots: one wavefront
+// per slot (a workgroup of its own: 14 slots of 1024 rows by four waves in turn took 20 us,
+// at once 6), each lane a Neumaier-compensated strided sum, then a fixed shuffle tree.
+__global__ __launch_bounds__(64) void finalize_kernel(const double *partials, int nblocks, ReduceArgs a,
+                                                      double *out)
+{
+    const int lane = threadIdx.x, s = blockIdx.x, part = s & 1;
+    const ObsDev ob = a.obs[s >> 1];
+    if (part && !obs_complex(ob.kind)) return;
+    double acc = 0.0, comp = 0.0;
+#pragma unroll 4
+    for (int b = lane; b < nblocks; b += 64) {
+        const double x = partials[(size_t)b * (2 * kMaxObs) + s];
+        const double t = acc + x;
+        comp += (fabs(acc) >= fabs(x)) ? (acc - t) + x : (x - t) + acc;
+        acc = t;
+    }
+    const double tot = wave_sum(acc + comp);
+    if (lane == 0) out[ob.slot + part] = tot;
 }
 
 // Batched observables: blockIdx.y = chain, the chain's vector split over gridDim.x blocks;
@@ -2806,16 +2876,36 @@ hipError_t launch_resident_factors(int n, int n_phases, const double *tab, doubl
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_reduce(int dtype, const ReduceArgs &a, double *partials, int nblocks,
-                         double *out, hipStream_t s)
+template <typename R>
+static hipError_t launch_reduce_r(const ReduceArgs &a, double *partials, int nblocks, hipStream_t s)
 {
-    if (dtype == 0)
-        hipLaunchKernelGGL((reduce_kernel<double>), dim3(nblocks), dim3(kThreads), 0, s, a, partials);
+    // accumulators live in registers: as few as the request needs
+    if (a.n_obs <= 2)
+        hipLaunchKernelGGL((reduce_kernel<R, 2>), dim3(nblocks), dim3(kThreads), 0, s, a, partials);
+    else if (a.n_obs <= 8)
+        hipLaunchKernelGGL((reduce_kernel<R, 8>), dim3(nblocks), dim3(kThreads), 0, s, a, partials);
     else
-        hipLaunchKernelGGL((reduce_kernel<float>), dim3(nblocks), dim3(kThreads), 0, s, a, partials);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kThreads), 0, s, partials, nblocks, a, out);
+        hipLaunchKernelGGL((reduce_kernel<R, kMaxObs>), dim3(nblocks), dim3(kThreads), 0, s, a, partials);
+    return hipGetLastError();
+}
+
+hipError_t launch_reduce(int dtype, const ReduceArgs &a, double *partials, int nblocks, hipStream_t s)
+{
+    if (a.n_obs < 1 || a.n_obs > kMaxObs) return hipErrorInvalidValue;
+    return dtype == 0 ? launch_reduce_r<double>(a, partials, nblocks, s)
+                      : launch_reduce_r<float>(a, partials, nblocks, s);
+}
+
+hipError_t launch_energy(int dtype, const void *psi, const EnergyPass &p, bool first, double *partials, int nblocks,
+                         hipStream_t s)
+{
+    if (p.T < 1 || p.T > energy_tile_bits(dtype) || p.n_ops < 0 || !p.ops || nblocks < 1) return hipErrorInvalidValue;
+    if (dtype == 0)
+        hipLaunchKernelGGL((energy_kernel<double, energy_tile_bits(0)>), dim3(nblocks), dim3(kThreads), 0, s,
+                           static_cast<const double2 *>(psi), p, (int)first, partials);
+    else
+        hipLaunchKernelGGL((energy_kernel<float, energy_tile_bits(1)>), dim3(nblocks), dim3(kThreads), 0, s,
+                           static_cast<const float2 *>(psi), p, (int)first, partials);
     return hipGetLastError();
 }
 
@@ -3020,7 +3110,7 @@ hipError_t launch_finalize(const double *partials, int nblocks, const ReduceArgs
         partials = tmp;
         nblocks = groups;
     }
-    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(kThreads), 0, s, partials, nblocks, a, out);
+    hipLaunchKernelGGL(finalize_kernel, dim3(2 * a.n_obs), dim3(64), 0, s, partials, nblocks, a, out);
     return hipGetLastError();
 }
 

@@ -273,14 +273,36 @@ __host__ __device__ constexpr bool obs_complex(int kind) { return kind == kObsOv
 
 struct ReduceArgs {
     const void *psi[kMaxVec];
-    ObsDev obs[kMaxObs];
+    ObsDev obs[kMaxObs];      // the energy's column is left to launch_energy
     int32_t n_obs;
     int32_t n;
-    // the Hamiltonian, for the energy observable: fields [n][3] (x, y, z) and merged bonds
-    const double *ham_h;
-    const HamBond *ham_b;
-    int32_t ham_nb;
 };
+
+// <psi|H|psi> (H of Sec. 2, Eq. 1) in passes over the state: a pass holds tiles of 2^T
+// amplitudes in LDS and takes every bond whose two spins are tile bits (each bond in one
+// pass), together with the fields of its spins where no bond before took them.  One op: over
+// the four amplitudes c_00, c_10, c_01, c_11 (bit of tile bit a first) of every pair of bits,
+// with S^x flipping a spin with amplitude 1/2 and S^y with +i/2 from down to up,
+//   w[0] |c_00|^2 + w[1] |c_10|^2 + w[2] |c_01|^2 + w[3] |c_11|^2        (z terms)
+//   + cA Re(conj(c_00) c_11) + cB Re(conj(c_10) c_01),  cA, cB = (J^x -+ J^y) / 2
+//   + hx Re(conj(c) u) - hy Im(conj(c) u) over the pairs (c, u) that flip a, then b, up.
+// b < 0 (one spin): the two amplitudes of bit a, w[0], w[1] and its flip.
+struct EnergyOp {
+    int32_t a, b, flips, pad;   // flips: some hx or hy is not zero
+    double w[4], cA, cB, hx[2], hy[2];
+};
+constexpr int energy_tile_bits(int dtype) { return dtype == 0 ? 11 : 12; }   // 32 KiB of LDS
+constexpr int kEnergyRuns = 16;
+struct EnergyPass {
+    Run tile_runs[kEnergyRuns], out_runs[kEnergyRuns];
+    int32_t n_tile_runs, n_out_runs;
+    int32_t T, n_ops;           // T = min(n, energy_tile_bits)
+    uint64_t n_tiles;
+    const EnergyOp *ops;
+};
+// Adds (first: writes) workgroup b's sum of the pass to partials[b * 2 * kMaxObs], b < nblocks.
+hipError_t launch_energy(int dtype, const void *psi, const EnergyPass &p, bool first, double *partials, int nblocks,
+                         hipStream_t s);
 
 // Adjoint: parameters of one axis whose gradient a reduction accumulates; pj < 0 marks a
 // field on spin pi, otherwise a coupling of spins pi and pj.  Workgroup b adds
@@ -414,8 +436,9 @@ hipError_t launch_resident(int dtype, const ResidentArgs &a, int nvec, hipStream
 hipError_t launch_resident_phases(const ResidentPhaseArgs &a, int nchains, hipStream_t s);
 // The factors of one system's phase tables `tab`.
 hipError_t launch_resident_factors(int n, int n_phases, const double *tab, double *fac, hipStream_t s);
-hipError_t launch_reduce(int dtype, const ReduceArgs &a, double *partials, int nblocks,
-                         double *out, hipStream_t s);
+// Sums of the observables per workgroup into partials [nblocks][2 * kMaxObs]; launch_finalize
+// then sums the rows.
+hipError_t launch_reduce(int dtype, const ReduceArgs &a, double *partials, int nblocks, hipStream_t s);
 
 // Fixed reduction scratch of the allocation-free entry point (ts_expect_noalloc): the
 // per-workgroup partials of at most kScratchBlocks workgroups, 2 * kMaxObs doubles each

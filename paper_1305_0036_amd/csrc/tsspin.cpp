@@ -157,7 +157,10 @@ struct ts_ctx {
     DevBuf adj_pad_buf;
     DevBuf unit_phase;     // one (1, 0) factor row for sweeps whose phase step has no energy
     DevBuf etab[2][3];     // energy tables D_axis(b) per dtype (double / float) and axis
-    DevBuf ham_h, ham_b;   // fields [n][3] and merged bonds (tsk::HamBond) for the energy
+    DevBuf ham_h, ham_b;   // fields [n][3] and merged bonds (tsk::HamBond) of H (ham_dev)
+    // the energy observable per dtype: its passes and their ops (device)
+    std::vector<tsk::EnergyPass> energy_passes[2];
+    DevBuf energy_ops[2];
     // batch context: one sub-context per chain (empty for a single system)
     std::vector<std::unique_ptr<ts_ctx>> chains;
     std::map<std::string, std::unique_ptr<struct BatchProgram>> programs;
@@ -1616,6 +1619,114 @@ ts_status ham_dev(ts_ctx *c)
     return TS_OK;
 }
 
+// Passes of the energy observable (tsk::EnergyPass): tiles of bit sets that together hold both
+// spins of every bond.  The first pass takes the lowest bits; each further one the lowest bits
+// of a run (128 bytes) and then, bit by bit, the one that brings in most bonds not yet taken, or
+// the two spins of the first such bond.  A chain of 24 spins takes three passes in complex128.
+ts_status energy_passes(ts_ctx *c, int dtype)
+{
+    if (!c->energy_passes[dtype].empty()) return TS_OK;
+    const int n = c->n, T = std::min(n, tsk::energy_tile_bits(dtype)), s = min_run_bits(dtype);
+    struct Bond { int i, j; std::array<double, 3> J; };
+    std::vector<Bond> left;
+    uint64_t bonded = 0;
+    for (size_t k = 0; k < c->bi.size(); ++k) {
+        left.push_back({c->bi[k], c->bj[k], c->J[k]});
+        bonded |= (1ull << c->bi[k]) | (1ull << c->bj[k]);
+    }
+    // a spin without bonds has its fields taken with a neighbour
+    for (int q = 0; q < n && n > 1; ++q)
+        if (!((bonded >> q) & 1)) left.push_back({std::min(q, q + 1 < n ? q + 1 : q - 1),
+                                                  std::max(q, q + 1 < n ? q + 1 : q - 1), {0.0, 0.0, 0.0}});
+    std::vector<std::pair<uint64_t, std::vector<tsk::EnergyOp>>> passes;
+    uint64_t fields_left = (1ull << n) - 1;
+    while (!left.empty() || passes.empty()) {
+        uint64_t S = (1ull << (passes.empty() ? T : std::min(s, T))) - 1;
+        auto gain = [&](uint64_t set) {
+            int g = 0;
+            for (const Bond &b : left) g += ((set >> b.i) & 1) && ((set >> b.j) & 1);
+            return g;
+        };
+        while (__builtin_popcountll(S) < T) {
+            int best = -1, bg = gain(S);
+            for (int q = 0; q < n; ++q)
+                if (!((S >> q) & 1) && gain(S | (1ull << q)) > bg) best = q, bg = gain(S | (1ull << q));
+            uint64_t add = best >= 0 ? 1ull << best : 0;
+            for (size_t k = 0; k < left.size() && !add; ++k) {
+                const uint64_t two = ((1ull << left[k].i) | (1ull << left[k].j)) & ~S;
+                if (two && __builtin_popcountll(S | two) <= T) add = two;
+            }
+            for (int q = 0; q < n && !add; ++q)   // nothing left to bring in: the lowest bits
+                if (!((S >> q) & 1)) add = 1ull << q;
+            S |= add;
+        }
+        std::vector<tsk::EnergyOp> ops;
+        auto tile_bit = [&](int q) { return __builtin_popcountll(S & ((1ull << q) - 1)); };
+        auto take_fields = [&](tsk::EnergyOp &o, int which, int q) {
+            if (!((fields_left >> q) & 1)) return;
+            fields_left &= ~(1ull << q);
+            o.hx[which] = c->h[q][0];
+            o.hy[which] = c->h[q][1];
+            o.flips = o.flips || o.hx[which] != 0.0 || o.hy[which] != 0.0;
+            for (int k = 0; k < 4; ++k) o.w[k] += ((k >> which) & 1) ? 0.5 * c->h[q][2] : -0.5 * c->h[q][2];
+        };
+        std::vector<Bond> rest;
+        for (const Bond &b : left) {
+            if (!((S >> b.i) & 1) || !((S >> b.j) & 1)) {
+                rest.push_back(b);
+                continue;
+            }
+            tsk::EnergyOp o{};
+            o.a = tile_bit(b.i);
+            o.b = tile_bit(b.j);
+            for (int k = 0; k < 4; ++k) o.w[k] = (k == 0 || k == 3 ? 0.25 : -0.25) * b.J[2];
+            o.cA = 0.5 * (b.J[0] - b.J[1]);
+            o.cB = 0.5 * (b.J[0] + b.J[1]);
+            take_fields(o, 0, b.i);
+            take_fields(o, 1, b.j);
+            ops.push_back(o);
+        }
+        if (n == 1) {
+            tsk::EnergyOp o{};
+            o.b = -1;
+            take_fields(o, 0, 0);
+            ops.push_back(o);
+        }
+        if (!passes.empty() && rest.size() == left.size()) return fail(TS_EINVAL, "energy passes: no progress");
+        left.swap(rest);
+        passes.push_back({S, std::move(ops)});
+    }
+    std::vector<tsk::EnergyOp> all;
+    for (const auto &p : passes) all.insert(all.end(), p.second.begin(), p.second.end());
+    ts_status st = alloc(c->energy_ops[dtype], all.size() * sizeof(tsk::EnergyOp));
+    if (st != TS_OK) return st;
+    TS_HIP(hipMemcpy(c->energy_ops[dtype].p, all.data(), all.size() * sizeof(tsk::EnergyOp), hipMemcpyHostToDevice));
+    std::vector<tsk::EnergyPass> out;
+    size_t at = 0;
+    for (const auto &p : passes) {
+        tsk::EnergyPass e{};
+        auto runs = [](uint64_t mask, tsk::Run *r, int32_t *nr) {
+            const auto rs = ts::deposit_runs(mask);
+            if (rs.size() > (size_t)tsk::kEnergyRuns) return false;
+            *nr = (int32_t)rs.size();
+            for (size_t i = 0; i < rs.size(); ++i)
+                r[i] = tsk::Run{(int8_t)rs[i].src, (int8_t)rs[i].len, (int8_t)rs[i].dst, 0};
+            return true;
+        };
+        if (!runs(p.first, e.tile_runs, &e.n_tile_runs) ||
+            !runs(((1ull << n) - 1) & ~p.first, e.out_runs, &e.n_out_runs))
+            return fail(TS_EINVAL, "energy passes: too many runs");
+        e.T = T;
+        e.n_ops = (int)p.second.size();
+        e.n_tiles = 1ull << (n - T);
+        e.ops = static_cast<const tsk::EnergyOp *>(c->energy_ops[dtype].p) + at;
+        at += p.second.size();
+        out.push_back(e);
+    }
+    c->energy_passes[dtype] = std::move(out);
+    return TS_OK;
+}
+
 ts_status reduce(ts_ctx *c, int dtype, const void *const *vecs, int nvec,
                  const std::vector<tsk::ObsDev> &obs, double *out, hipStream_t stream)
 {
@@ -1624,23 +1735,29 @@ ts_status reduce(ts_ctx *c, int dtype, const void *const *vecs, int nvec,
     for (size_t k = 0; k < obs.size(); ++k) ra.obs[k] = obs[k];
     ra.n_obs = (int)obs.size();
     ra.n = c->n;
-    ts_status st;
-    for (const auto &o : obs)
-        if (o.kind == TS_OBS_ENERGY) {
-            st = ham_dev(c);
-            if (st != TS_OK) return st;
-            ra.ham_h = static_cast<const double *>(c->ham_h.p);
-            ra.ham_b = static_cast<const tsk::HamBond *>(c->ham_b.p);
-            ra.ham_nb = (int)c->bi.size();
-            break;
-        }
-    st = alloc(c->partials, (size_t)kRedBlocks * 2 * tsk::kMaxObs * sizeof(double));
+    ts_status st = alloc(c->partials, (size_t)kRedBlocks * 2 * tsk::kMaxObs * sizeof(double));
     if (st != TS_OK) return st;
     const uint64_t dim = 1ull << c->n;
     uint64_t nb = dim / (256 * 4);
     if (nb < 1) nb = 1;
     if (nb > (uint64_t)kRedBlocks) nb = kRedBlocks;
-    TS_HIP(tsk::launch_reduce(dtype, ra, static_cast<double *>(c->partials.p), (int)nb, out, stream));
+    double *parts = static_cast<double *>(c->partials.p);
+    bool others = false;
+    for (size_t k = 0; k < obs.size(); ++k) {
+        if (obs[k].kind != TS_OBS_ENERGY) {
+            others = true;
+            continue;
+        }
+        st = energy_passes(c, dtype);
+        if (st != TS_OK) return st;
+        bool first = true;
+        for (const tsk::EnergyPass &p : c->energy_passes[dtype]) {
+            TS_HIP(tsk::launch_energy(dtype, vecs[obs[k].ket], p, first, parts + 2 * k, (int)nb, stream));
+            first = false;
+        }
+    }
+    if (others) TS_HIP(tsk::launch_reduce(dtype, ra, parts, (int)nb, stream));
+    TS_HIP(tsk::launch_finalize(parts, (int)nb, ra, out, nullptr, stream));
     return TS_OK;
 }
 
@@ -2505,7 +2622,8 @@ ts_status ts_expect_noalloc(ts_ctx *ctx, const void *psi, ts_dtype dtype, const 
     double *scr = nullptr;
     TS_HIP(tsk::scratch_address(&scr));
     // every partial the finalize step reads is written by this call's reduction first
-    TS_HIP(tsk::launch_reduce(dtype, ra, scr, (int)nb, out_dev, static_cast<hipStream_t>(stream)));
+    TS_HIP(tsk::launch_reduce(dtype, ra, scr, (int)nb, static_cast<hipStream_t>(stream)));
+    TS_HIP(tsk::launch_finalize(scr, (int)nb, ra, out_dev, nullptr, static_cast<hipStream_t>(stream)));
     return TS_OK;
 }
 
