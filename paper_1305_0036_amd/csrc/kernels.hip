@@ -1009,8 +1009,16 @@ __device__ __forceinline__ void cone_transpose_pair(V (&x)[1 << RB], V (&y)[1 <<
     }
 }
 
-template <typename V>
-__device__ __forceinline__ void apply_cone(V &x, double2 z) { apply_phase(x, z); }
+// apply_phase in place: the same four operations, with the results tied to the amplitude's
+// registers.  Left to itself the compiler writes the products of a whole phase step to other
+// registers and copies them back at the end of the stage (32 moves, and 64 registers more).
+__device__ __forceinline__ void apply_cone(double2 &x, double2 z)
+{
+    const double t = x.y * z.y, u = x.y * z.x;
+    asm("v_fma_f64 %0, %1, %2, %3" : "+v"(x.y) : "v"(x.x), "v"(z.y), "v"(u));
+    asm("v_fma_f64 %0, %0, %1, -%2" : "+v"(x.x) : "v"(z.x), "v"(t));
+}
+__device__ __forceinline__ void apply_cone(float2 &x, double2 z) { apply_phase(x, z); }
 
 // Row of a phase step's workgroup table that this tile selects (its outside spins).
 __device__ __forceinline__ uint64_t cone_row(const ConePhaseArgs &ph, uint64_t tile)
@@ -1020,127 +1028,6 @@ __device__ __forceinline__ uint64_t cone_row(const ConePhaseArgs &ph, uint64_t t
     for (int b = 0; b < ph.n_row_bits; ++b)
         row |= ((tile >> ((rb[b >> 2] >> (8 * (b & 3))) & 0xffu)) & 1ull) << b;
     return row;
-}
-
-// Phase step of a light-cone sweep in window w.  Each step holds few terms, so the product is
-// built only from its non-trivial parts: the thread table entry and the workgroup row entry
-// (which already hold the couplings and row fields of the window bits with every window bit
-// down), the row-dependent fields of the thread bits in xmask, the Gray-code walk over the
-// window bits (flipping bit v up multiplies by the square of its two factors); then one
-// window-table factor per register.  The walk always runs: a step without such couplings
-// has walk factors of exactly 1 + 0i (its tables hold exp(0) there), whose products are
-// exact, and a branch on it becomes selects on every register of the walk.  wgf is the
-// workgroup's row of the step (w0: its entry 0 times the step's scalar), q the window table.
-template <int T, int RB, typename V>
-__device__ __forceinline__ void cone_diag(V (&x)[1 << RB], ctab wgf, double2 w0, ctab q,
-                                          const double2 (&th)[1 + RB], uint32_t xmask, int w)
-{
-    const uint32_t tid = threadIdx.x;
-    const uint32_t t0 = thread_part<RB>(tid, w);
-    double2 p = cmul(w0, th[0]);
-    uint32_t m = xmask & ~(((1u << RB) - 1u) << w);
-    while (m) {
-        const int k = __builtin_ctz(m);
-        m &= m - 1u;
-        const double2 G = ld2(wgf, 1 + k);
-        p = cmul(p, ((t0 >> k) & 1) ? G : make_double2(G.x, -G.y));
-    }
-    double2 wv[RB];
-#pragma unroll
-    for (int v = 0; v < RB; ++v) wv[v] = cmul(ld2(wgf, 1 + w + v), th[1 + v]);
-#pragma unroll
-    for (int k = 0; k < (1 << RB); ++k) {
-        const int j = k ^ (k >> 1);
-        if (k > 0) {
-            const int v = __builtin_ctz(k);
-            p = cmul(p, ((j >> v) & 1) ? wv[v] : make_double2(wv[v].x, -wv[v].y));
-        }
-        apply_cone(x[j], cmul(p, ld2(q, j)));
-    }
-}
-
-// The same phase step when only the window bits in CM (known when compiling) have walk
-// factors other than exactly 1 + 0i: instead of the Gray-code walk over all 2^RB registers,
-// the products P[s] = p * prod_{v in s} wv[v] over the subsets s of CM (2^|CM| - 1 complex
-// products), and register j takes P[j & CM] * q[j].  Most light-cone steps of a chain couple
-// one or two window bits to the rest of the tile (bonds at the window's edges).
-template <int T, int RB, uint32_t CM, typename V>
-__device__ __forceinline__ void cone_diag_cm(V (&x)[1 << RB], ctab wgf, double2 w0, ctab q,
-                                             const double2 (&th)[1 + RB], uint32_t xmask, int w)
-{
-    const uint32_t t0 = thread_part<RB>(threadIdx.x, w);
-    double2 P[1 << RB];
-    P[0] = cmul(w0, th[0]);
-    uint32_t m = xmask & ~(((1u << RB) - 1u) << w);
-    while (m) {
-        const int k = __builtin_ctz(m);
-        m &= m - 1u;
-        const double2 G = ld2(wgf, 1 + k);
-        P[0] = cmul(P[0], ((t0 >> k) & 1) ? G : make_double2(G.x, -G.y));
-    }
-#pragma unroll
-    for (int v = 0; v < RB; ++v) {
-        if (!((CM >> v) & 1u)) continue;
-        const double2 f = cmul(ld2(wgf, 1 + w + v), th[1 + v]);
-        const uint32_t lower = CM & ((1u << v) - 1u);
-#pragma unroll
-        for (uint32_t s = 0; s < (1u << RB); ++s)
-            if ((s & ~lower) == 0) P[s | (1u << v)] = cmul(P[s], f);
-    }
-#pragma unroll
-    for (int j = 0; j < (1 << RB); ++j) apply_cone(x[j], cmul(P[j & CM], ld2(q, j)));
-}
-
-// ... on two vectors (the adjoint's psi and lambda), each factor formed once.  Its own copy
-// of the products: sharing them with the one-vector form through a helper made the compiler
-// keep part of that form's register array in scratch memory.
-template <int T, int RB, uint32_t CM, typename V>
-__device__ __forceinline__ void cone_diag_cm_pair(V (&x)[1 << RB], V (&y)[1 << RB], const double2 *wgf,
-                                                  const double2 *q, const double2 (&th)[1 + RB],
-                                                  uint32_t xmask, int w)
-{
-    const uint32_t t0 = thread_part<RB>(threadIdx.x, w);
-    double2 P[1 << RB];
-    P[0] = cmul(wgf[0], th[0]);
-    uint32_t m = xmask & ~(((1u << RB) - 1u) << w);
-    while (m) {
-        const int k = __builtin_ctz(m);
-        m &= m - 1u;
-        const double2 G = wgf[1 + k];
-        P[0] = cmul(P[0], ((t0 >> k) & 1) ? G : make_double2(G.x, -G.y));
-    }
-#pragma unroll
-    for (int v = 0; v < RB; ++v) {
-        if (!((CM >> v) & 1u)) continue;
-        const double2 f = cmul(wgf[1 + w + v], th[1 + v]);
-        const uint32_t lower = CM & ((1u << v) - 1u);
-#pragma unroll
-        for (uint32_t s = 0; s < (1u << RB); ++s)
-            if ((s & ~lower) == 0) P[s | (1u << v)] = cmul(P[s], f);
-    }
-#pragma unroll
-    for (int j = 0; j < (1 << RB); ++j) {
-        const double2 z = cmul(P[j & CM], q[j]);
-        apply_cone(x[j], z);
-        apply_cone(y[j], z);
-    }
-}
-
-// One phase step of the adjoint light-cone sweep on psi and lambda: the specialised walk
-// masks, else subset products over all four bits (the Gray-code walk on two vectors does
-// not fit the registers).
-template <int T, int RB, typename V>
-__device__ __forceinline__ void cone_phase_pair(V (&x)[1 << RB], V (&y)[1 << RB], const ConePhaseArgs &ph,
-                                                const double2 *wp, const double2 *qp,
-                                                const double2 (&th)[1 + RB], int w)
-{
-    switch (ph.cmask) {
-    case 0: cone_diag_cm_pair<T, RB, 0u>(x, y, wp, qp, th, ph.xmask, w); break;
-    case 1: cone_diag_cm_pair<T, RB, 1u>(x, y, wp, qp, th, ph.xmask, w); break;
-    case 8: cone_diag_cm_pair<T, RB, 8u>(x, y, wp, qp, th, ph.xmask, w); break;
-    case 9: cone_diag_cm_pair<T, RB, 9u>(x, y, wp, qp, th, ph.xmask, w); break;
-    default: cone_diag_cm_pair<T, RB, 15u>(x, y, wp, qp, th, ph.xmask, w); break;
-    }
 }
 
 // The phase tables are reached through pointers stored in the sweep arguments; these name
@@ -1160,6 +1047,137 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v)
 __device__ __forceinline__ double2 gload2(gtab t, size_t i)
 {
     return make_double2(t[2 * i], t[2 * i + 1]);
+}
+
+// Phase step of a light-cone sweep in window w.  Each step holds few terms, so the product is
+// built only from its non-trivial parts: the thread table entry and the workgroup row entry
+// (which already hold the couplings and row fields of the window bits with every window bit
+// down), the row-dependent fields of the thread bits in xmask, per window bit the factor that
+// flips it up (exactly 1 + 0i for a bit without thread or row couplings), and one window-table
+// factor per register.  Most light-cone steps of a chain couple the lowest or the highest
+// window bit, or both, to the rest of the tile (bonds at the window's edges): register j takes
+// P[lowest bit of j, highest bit of j] * q[j].  One code path serves every such mask, and the
+// inner bits of other masks come in beside it: with a copy of the loop per mask the
+// compiler moved the amplitudes to other registers and back around them (32 to 64 moves per
+// step, and as many registers more).  wgf is the workgroup's row of the step (w0: its entry 0 times the step's
+// scalar), q the window table, row the thread's table row.
+template <int T, int RB, typename V>
+__device__ __forceinline__ void cone_diag(V (&x)[1 << RB], ctab wgf, double2 w0, ctab q, const double2 (&th)[3],
+                                          uint32_t cmask, uint32_t xmask, gtab row, int w)
+{
+    constexpr uint32_t HI = 1u << (RB - 1);
+    const uint32_t t0 = thread_part<RB>(threadIdx.x, w);
+    double2 P[4];
+    P[0] = cmul(w0, th[0]);
+    uint32_t m = xmask & ~(((1u << RB) - 1u) << w);
+    while (m) {
+        const int k = __builtin_ctz(m);
+        m &= m - 1u;
+        const double2 G = ld2(wgf, 1 + k);
+        P[0] = cmul(P[0], ((t0 >> k) & 1) ? G : make_double2(G.x, -G.y));
+    }
+    P[1] = P[0];
+    if (cmask & 1u) P[1] = cmul(P[0], cmul(ld2(wgf, 1 + w), th[1]));
+    P[2] = P[0];
+    P[3] = P[1];
+    if (cmask & HI) {
+        const double2 f = cmul(ld2(wgf, RB + w), th[2]);
+        P[2] = cmul(P[0], f);
+        P[3] = cmul(P[1], f);
+    }
+    const bool inner = (cmask & ~(1u | HI)) != 0;
+    auto bit_factor = [&](int v) { return cmul(ld2(wgf, 1 + w + v), gload2(row, 1 + v)); };
+    if constexpr (std::is_same<V, double2>::value) {
+        // complex128: the inner bits' factors first (113 registers: four waves per SIMD)
+        if (inner) {
+#pragma unroll
+            for (int v = 1; v < RB - 1; ++v) {
+                if (!((cmask >> v) & 1u)) continue;
+                const double2 f = bit_factor(v);
+#pragma unroll
+                for (int j = 0; j < (1 << RB); ++j)
+                    if ((j >> v) & 1) apply_cone(x[j], f);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < (1 << RB); ++j) {
+            apply_cone(x[j], cmul(P[(j & 1) | ((j >> (RB - 1)) << 1)], ld2(q, j)));
+            if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+    } else {
+        // complex64: one product and one rounding per amplitude whatever the mask; the four
+        // registers that share their inner bits together
+#pragma unroll
+        for (int i = 0; i < (1 << (RB - 2)); ++i) {
+            double2 z[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) z[e] = cmul(P[e], ld2(q, (e & 1) | (i << 1) | ((e >> 1) << (RB - 1))));
+            if (i > 0 && inner) {
+#pragma unroll
+                for (int v = 1; v < RB - 1; ++v) {
+                    if (!((i >> (v - 1)) & 1)) continue;
+                    const double2 f = bit_factor(v);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) z[e] = cmul(z[e], f);
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) apply_cone(x[(e & 1) | (i << 1) | ((e >> 1) << (RB - 1))], z[e]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+}
+
+// ... on two vectors (the adjoint's psi and lambda), each factor formed once; the row and the
+// window table are in LDS.
+template <int T, int RB, typename V>
+__device__ __forceinline__ void cone_phase_pair(V (&x)[1 << RB], V (&y)[1 << RB], const ConePhaseArgs &ph,
+                                                const double2 *wgf, const double2 *q,
+                                                const double2 (&th)[1 + RB], int w)
+{
+    constexpr uint32_t HI = 1u << (RB - 1);
+    const uint32_t t0 = thread_part<RB>(threadIdx.x, w), cmask = ph.cmask;
+    double2 P[4];
+    P[0] = cmul(wgf[0], th[0]);
+    uint32_t m = ph.xmask & ~(((1u << RB) - 1u) << w);
+    while (m) {
+        const int k = __builtin_ctz(m);
+        m &= m - 1u;
+        const double2 G = wgf[1 + k];
+        P[0] = cmul(P[0], ((t0 >> k) & 1) ? G : make_double2(G.x, -G.y));
+    }
+    P[1] = P[0];
+    if (cmask & 1u) P[1] = cmul(P[0], cmul(wgf[1 + w], th[1]));
+    P[2] = P[0];
+    P[3] = P[1];
+    if (cmask & HI) {
+        const double2 f = cmul(wgf[RB + w], th[RB]);
+        P[2] = cmul(P[0], f);
+        P[3] = cmul(P[1], f);
+    }
+    const bool inner = (cmask & ~(1u | HI)) != 0;
+#pragma unroll
+    for (int i = 0; i < (1 << (RB - 2)); ++i) {
+        double2 z[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = cmul(P[e], q[(e & 1) | (i << 1) | ((e >> 1) << (RB - 1))]);
+        if (i > 0 && inner) {
+#pragma unroll
+            for (int v = 1; v < RB - 1; ++v) {
+                if (!((i >> (v - 1)) & 1)) continue;
+                const double2 f = cmul(wgf[1 + w + v], th[1 + v]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) z[e] = cmul(z[e], f);
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const int j = (e & 1) | (i << 1) | ((e >> 1) << (RB - 1));
+            apply_cone(x[j], z[e]);
+            apply_cone(y[j], z[e]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
 }
 
 __device__ __forceinline__ double wave_sum(double v);
@@ -1292,6 +1310,22 @@ __device__ __forceinline__ void cone_thread_row(const ConeArgs *__restrict__ a, 
         if ((need >> v) & 1u) th[1 + v] = gload2(dt, (size_t)row * (1 + RB) + 1 + v);
 }
 
+// The same for the one-vector sweep: the row's address, entry 0, and the entries of the lowest
+// and the highest window bit where the step's walk mask is one of those two (or both); any
+// other mask loads its entries when it gets there (cone_diag).
+template <int RB>
+__device__ __forceinline__ gtab cone_thread_ends(const ConeArgs *__restrict__ a, uint32_t code, double2 (&th)[3])
+{
+    const uint32_t need = (code >> 15) & 15u;
+    uint32_t row = threadIdx.x;
+    asm volatile("" : "+v"(row));
+    const gtab dt = as_global(a->ph[(code >> 9) & 63u].dtab) + 2 * (size_t)row * (1 + RB);
+    th[0] = gload2(dt, 0);
+    if (need & 1u) th[1] = gload2(dt, 1);
+    if ((need >> (RB - 1)) & 1u) th[2] = gload2(dt, RB);
+    return dt;
+}
+
 // Reads one word of every 64-byte line of every phase step's workgroup row and window table,
 // right behind the tile's loads: the steps' own scalar loads then hit the scalar cache.  (A
 // launch of few workgroups per CU has too few waves to hide a trip to L2 at every step.)
@@ -1351,8 +1385,9 @@ __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
         const int p = (int)((code >> 9) & 63u);
         // the thread's phase-table row is loaded first: its latency then hides behind the
         // transpose and the butterflies of the stage
-        double2 th[1 + RB];
-        if (has_phase) cone_thread_row<RB>(a, code, th);
+        double2 th[3];
+        gtab row = nullptr;
+        if (has_phase) row = cone_thread_ends<RB>(a, code, th);
         if (w != cur) {
             cone_transpose<RB>(x, lds, cur, w);
             cur = w;
@@ -1366,13 +1401,7 @@ __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
             const ctab wp = as_const(ph.wgf) + 2 * cone_row(ph, tile) * (T + 1);
             const double2 w0 = cmul(make_double2(ph.kre, ph.kim), ld2(wp, 0));
             const ctab qp = as_const(ph.dtab) + 2 * (1u << (T - RB)) * (1 + RB);
-            switch (ph.cmask) {
-            case 0: cone_diag_cm<T, RB, 0u>(x, wp, w0, qp, th, ph.xmask, w); break;
-            case 1: cone_diag_cm<T, RB, 1u>(x, wp, w0, qp, th, ph.xmask, w); break;
-            case 8: cone_diag_cm<T, RB, 8u>(x, wp, w0, qp, th, ph.xmask, w); break;
-            case 9: cone_diag_cm<T, RB, 9u>(x, wp, w0, qp, th, ph.xmask, w); break;
-            default: cone_diag<T, RB>(x, wp, w0, qp, th, ph.xmask, w); break;
-            }
+            cone_diag<T, RB>(x, wp, w0, qp, th, ph.cmask, ph.xmask, row, w);
         }
     }
     if (cur != a->store_win) cone_transpose<RB>(x, lds, cur, a->store_win);
@@ -1396,7 +1425,7 @@ __host__ __device__ constexpr size_t cone_tab_bytes(int n_phases)
 // complex128 transposes through the half buffer; three waves per SIMD (at 128 registers,
 // which four would need, the compiler spills).  complex64 runs four workgroups per CU.
 template <int T, int RB>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(4)))
 void cone_c128_kernel(double2 *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
                       int reverse)
 {
@@ -1419,7 +1448,7 @@ void cone_c64_kernel(float2 *__restrict__ psi, const ConeArgs *__restrict__ a, u
 
 // The last sweep of a vector's recorded segment, with the segment's observables.
 template <int T, int RB>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(4)))
 void cone_rec_c128_kernel(double2 *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
                           int reverse, ConeRec rec)
 {
@@ -1609,7 +1638,7 @@ __global__ __launch_bounds__(1 << (T - RB)) void cone_pair_c64_kernel(float2 *__
 // args[c].  (Both are derived from kernel arguments, so the stage loop keeps its scalar
 // loads and the state accesses stay global ones; pointers read from memory lose both.)
 template <typename R, int T, int RB>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(4)))
 void cone_batch_kernel(typename Vec<R>::T *__restrict__ packed, const int64_t *__restrict__ off,
                        const ConeArgs *__restrict__ args, uint64_t tiles_per_chain, int reverse)
 {
