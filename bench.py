@@ -481,7 +481,7 @@ def run_dtype(torch, tsspin, w, a0, c0, name, K, Wm, ref):
     kernel_only_ms = f0.elapsed_time(f1) / l1
     cfg = H.kernel_config(code, 4)
     if cone:
-        kname = f"cone_{name}_kernel<{cfg['tile_bits']}, 4> (light-cone sweeps)"
+        kname = f"cone_kernel<{'double' if name == 'c128' else 'float'}, {cfg['tile_bits']}, 4> (light-cone sweeps)"
     else:
         v = 3 if (cfg["variant"] == 4 and name == "c128") else (0 if cfg["variant"] == 4 else cfg["variant"])
         kname = (f"{'sweep_pipe_kernel' if v == 2 else 'sweep_reg_kernel'}"

@@ -201,12 +201,12 @@ __device__ void build_qtab(double2 *qtab, const DiagArgs &d, const double *jt)
     }
 }
 
-// Phase step on the thread's 2^(T-8) amplitudes t = tid + 256*j of the LDS tile.
+// Factors z of a phase step for the thread's 2^(T-8) amplitudes t = tid + 256*j of a tile, use(t, z).
 // wg = [C, geff_0 .. geff_{T-1}] of this workgroup, jt = tile couplings (upper triangle),
 // b_thread = global index of element j = 0.
-template <int T, typename V>
-__device__ void diag_step(V *tile, int ne, const DiagArgs &d, const double *wg, const double *jt,
-                          const double2 *qtab, uint64_t b_thread)
+template <int T, typename F>
+__device__ __forceinline__ void diag_factors(int ne, const DiagArgs &d, const double *wg, const double *jt,
+                                             const double2 *qtab, uint64_t b_thread, F use)
 {
     constexpr int NV = (T > kFixedBits) ? T - kFixedBits : 0;
     constexpr int EPT = 1 << NV;
@@ -252,11 +252,20 @@ __device__ void diag_step(V *tile, int ne, const DiagArgs &d, const double *wg, 
             const double2 wv = ((j >> v) & 1) ? w[v] : make_double2(w[v].x, -w[v].y);
             p = cmul(p, wv);
         }
-        const double2 z = cmul(p, qtab[j]);
-        V x = tile[tid + kThreads * j];
-        apply_phase(x, z);
-        tile[tid + kThreads * j] = x;
+        use(tid + kThreads * j, cmul(p, qtab[j]));
     }
+}
+
+// Phase step on the thread's amplitudes of the LDS tile.
+template <int T, typename V>
+__device__ void diag_step(V *tile, int ne, const DiagArgs &d, const double *wg, const double *jt,
+                          const double2 *qtab, uint64_t b_thread)
+{
+    diag_factors<T>(ne, d, wg, jt, qtab, b_thread, [&](int t, double2 z) {
+        V x = tile[t];
+        apply_phase(x, z);
+        tile[t] = x;
+    });
 }
 
 template <typename R, int T>
@@ -930,6 +939,22 @@ __device__ __forceinline__ void cone_transpose(V (&x)[1 << RB], V *lds, int from
     for (int r = 0; r < (1 << RB); ++r) x[r] = pt[r * mt];
 }
 
+// The same through two full buffers in turn (`lds`: the one that the transpose before did not
+// use): the barrier between has seen every wave past its reads of it, so one barrier is enough.
+template <int RB, typename V>
+__device__ __forceinline__ void cone_transpose_next(V (&x)[1 << RB], V *lds, int from, int to)
+{
+    const uint32_t tid = threadIdx.x;
+    const uint32_t bf = lds_pos(thread_part<RB>(tid, from)), bt = lds_pos(thread_part<RB>(tid, to));
+    const uint32_t mf = lds_pos(1u << from), mt = lds_pos(1u << to);
+    V *pf = lds + bf, *pt = lds + bt;
+#pragma unroll
+    for (int r = 0; r < (1 << RB); ++r) pf[r * mf] = x[r];
+    lds_barrier();
+#pragma unroll
+    for (int r = 0; r < (1 << RB); ++r) x[r] = pt[r * mt];
+}
+
 // complex128 through the half buffer: real parts, then imaginary parts
 template <int RB>
 __device__ __forceinline__ void cone_transpose(double2 (&x)[1 << RB], double *lds, int from, int to)
@@ -1061,7 +1086,7 @@ __device__ __forceinline__ double2 gload2(gtab t, size_t i)
 // compiler moved the amplitudes to other registers and back around them (32 to 64 moves per
 // step, and as many registers more).  wgf is the workgroup's row of the step (w0: its entry 0 times the step's
 // scalar), q the window table, row the thread's table row.
-template <int T, int RB, typename V>
+template <int T, int RB, bool FEW, typename V>
 __device__ __forceinline__ void cone_diag(V (&x)[1 << RB], ctab wgf, double2 w0, ctab q, const double2 (&th)[3],
                                           uint32_t cmask, uint32_t xmask, gtab row, int w)
 {
@@ -1102,28 +1127,38 @@ __device__ __forceinline__ void cone_diag(V (&x)[1 << RB], ctab wgf, double2 w0,
 #pragma unroll
         for (int j = 0; j < (1 << RB); ++j) {
             apply_cone(x[j], cmul(P[(j & 1) | ((j >> (RB - 1)) << 1)], ld2(q, j)));
-            if ((j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
+            if (!FEW && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
     } else {
-        // complex64: one product and one rounding per amplitude whatever the mask; the four
-        // registers that share their inner bits together
+        // complex64: one product and one rounding per amplitude whatever the mask, by the same
+        // operations for a given mask always (see resident_diag_kernel): the registers in
+        // Gray-code order, four at a time (FEW: all at once), and other masks walk along, P[0]
+        // the walk's factor (its steps formed where they are used: held, they would not fit the
+        // registers)
+        constexpr int G = FEW ? 1 << RB : 4;
 #pragma unroll
-        for (int i = 0; i < (1 << (RB - 2)); ++i) {
-            double2 z[4];
+        for (int k0 = 0; k0 < (1 << RB); k0 += G) {
+            double2 z[G];
+            if (inner) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) z[e] = cmul(P[e], ld2(q, (e & 1) | (i << 1) | ((e >> 1) << (RB - 1))));
-            if (i > 0 && inner) {
+                for (int e = 0; e < G; ++e) {
+                    const int k = k0 + e, j = k ^ (k >> 1), v = k ? __builtin_ctz(k) : 0;
+                    if (k > 0) {
+                        const double2 f = bit_factor(v);
+                        P[0] = cmul(P[0], ((j >> v) & 1) ? f : make_double2(f.x, -f.y));
+                    }
+                    z[e] = cmul(P[0], ld2(q, j));
+                }
+            } else {
 #pragma unroll
-                for (int v = 1; v < RB - 1; ++v) {
-                    if (!((i >> (v - 1)) & 1)) continue;
-                    const double2 f = bit_factor(v);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) z[e] = cmul(z[e], f);
+                for (int e = 0; e < G; ++e) {
+                    const int k = k0 + e, j = k ^ (k >> 1);
+                    z[e] = cmul(P[(j & 1) | ((j >> (RB - 1)) << 1)], ld2(q, j));
                 }
             }
 #pragma unroll
-            for (int e = 0; e < 4; ++e) apply_cone(x[(e & 1) | (i << 1) | ((e >> 1) << (RB - 1))], z[e]);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int e = 0; e < G; ++e) apply_cone(x[(k0 + e) ^ ((k0 + e) >> 1)], z[e]);
+            if (!FEW) __builtin_amdgcn_sched_barrier(0);
         }
     }
 }
@@ -1158,18 +1193,21 @@ __device__ __forceinline__ void cone_phase_pair(V (&x)[1 << RB], V (&y)[1 << RB]
     const bool inner = (cmask & ~(1u | HI)) != 0;
 #pragma unroll
     for (int i = 0; i < (1 << (RB - 2)); ++i) {
-        double2 z[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) z[e] = cmul(P[e], q[(e & 1) | (i << 1) | ((e >> 1) << (RB - 1))]);
-        if (i > 0 && inner) {
+        double2 z[4] = {P[0], P[1], P[2], P[3]};
+        if (i > 0 && inner) {  // the set bits' factors in ascending order
 #pragma unroll
             for (int v = 1; v < RB - 1; ++v) {
                 if (!((i >> (v - 1)) & 1)) continue;
                 const double2 f = cmul(wgf[1 + w + v], th[1 + v]);
-#pragma unroll
-                for (int e = 0; e < 4; ++e) z[e] = cmul(z[e], f);
+                z[0] = cmul(z[0], f);
+                z[1] = cmul(z[1], f);
             }
+            const double2 f = cmul(wgf[RB + w], th[RB]);
+            z[2] = cmul(z[0], f);
+            z[3] = cmul(z[1], f);
         }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) z[e] = cmul(z[e], q[(e & 1) | (i << 1) | ((e >> 1) << (RB - 1))]);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const int j = (e & 1) | (i << 1) | ((e >> 1) << (RB - 1));
@@ -1183,48 +1221,51 @@ __device__ __forceinline__ void cone_phase_pair(V (&x)[1 << RB], V (&y)[1 << RB]
 __device__ __forceinline__ double wave_sum(double v);
 
 // Observables of a recorded segment from the tile the last light-cone sweep of a vector is
-// about to store (its addresses gb | off[r] are the basis indices): FP64 sums over the
-// thread's amplitudes, register by register (one bra amplitude in flight at a time keeps the
-// register budget of the sweep), then a wave reduction and one row of partials per
-// workgroup.  At most kConeRecMax observables per vector.
+// about to store (its addresses gb | off[r] are the basis indices): one observable at a time,
+// FP64 sums over the thread's amplitudes (four bra amplitudes in flight: the register budget
+// of the sweep), then a wave reduction and one row of partials per workgroup.  (The kinds'
+// code once per register and observable was 60 KB of instructions that no cache kept.)  At
+// most kConeRecMax observables per vector.
 template <typename R, int RB>
 __device__ __forceinline__ void cone_record(const typename Vec<R>::T (&x)[1 << RB], uint64_t gb,
                                             const uint64_t *off, const ConeRec &rec, double *red)
 {
     using V = typename Vec<R>::T;
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-    double acc[kConeRecMax][2];
+#pragma unroll 1
+    for (int o = 0; o < rec.n_obs; ++o) {
+        const ObsDev ob = rec.obs[o];
+        double a0 = 0.0, a1 = 0.0;
+        if (obs_complex(ob.kind)) {
+            const V *bra = static_cast<const V *>(rec.bra[o]);
 #pragma unroll
-    for (int o = 0; o < kConeRecMax; ++o) acc[o][0] = acc[o][1] = 0.0;
+            for (int r = 0; r < (1 << RB); r += 4) {
+                V w[4];
 #pragma unroll
-    for (int r = 0; r < (1 << RB); ++r) {
-        const uint64_t b = gb | off[r];
-        const double cr = x[r].x, ci = x[r].y, p = cr * cr + ci * ci;
+                for (int e = 0; e < 4; ++e) w[e] = bra[gb | off[r + e]];
 #pragma unroll
-        for (int o = 0; o < kConeRecMax; ++o) {
-            if (o >= rec.n_obs) break;
-            const ObsDev ob = rec.obs[o];
-            switch (ob.kind) {
-            case 0: acc[o][0] += p; break;
-            case 3: acc[o][0] += (((b >> ob.i) & 1) ? 0.5 : -0.5) * p; break;
-            case 4: acc[o][0] += ((((b >> ob.i) ^ (b >> ob.j)) & 1) ? -0.25 : 0.25) * p; break;
-            case 5: acc[o][0] += ((double)__popcll(b) - 0.5 * rec.n) * p; break;
-            case kObsOverlapSz:
-            case kObsOverlap: {
-                const V w = static_cast<const V *>(rec.bra[o])[b];
-                const double s = ob.kind == kObsOverlap ? 1.0 : (((b >> ob.i) & 1) ? 0.5 : -0.5);
-                acc[o][0] += s * ((double)w.x * cr + (double)w.y * ci);
-                acc[o][1] += s * ((double)w.x * ci - (double)w.y * cr);
-                break;
+                for (int e = 0; e < 4; ++e) {
+                    const double cr = x[r + e].x, ci = x[r + e].y;
+                    const double s = ob.kind == kObsOverlap ? 1.0 : (((gb | off[r + e]) >> ob.i) & 1) ? 0.5 : -0.5;
+                    a0 += s * ((double)w[e].x * cr + (double)w[e].y * ci);
+                    a1 += s * ((double)w[e].x * ci - (double)w[e].y * cr);
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
-            default: break;
+        } else {
+#pragma unroll
+            for (int r = 0; r < (1 << RB); ++r) {
+                const uint64_t b = gb | off[r];
+                const double cr = x[r].x, ci = x[r].y;
+                double f = 1.0;
+                if (ob.kind == 3) f = ((b >> ob.i) & 1) ? 0.5 : -0.5;
+                if (ob.kind == 4) f = (((b >> ob.i) ^ (b >> ob.j)) & 1) ? -0.25 : 0.25;
+                if (ob.kind == 5) f = (double)__popcll(b) - 0.5 * rec.n;
+                a0 += f * (cr * cr + ci * ci);
             }
         }
-    }
-#pragma unroll
-    for (int o = 0; o < kConeRecMax; ++o) {
-        if (o >= rec.n_obs) break;
-        const double a0 = wave_sum(acc[o][0]), a1 = wave_sum(acc[o][1]);
+        a0 = wave_sum(a0);
+        a1 = wave_sum(a1);
         if (lane == 0) {
             red[2 * wv] = a0;
             red[2 * wv + 1] = a1;
@@ -1233,7 +1274,7 @@ __device__ __forceinline__ void cone_record(const typename Vec<R>::T (&x)[1 << R
         if (threadIdx.x < 2) {
             double sum = 0.0;
             for (int w = 0; w < nw; ++w) sum += red[2 * w + threadIdx.x];
-            rec.partials[(size_t)blockIdx.x * (2 * kMaxObs) + 2 * rec.obs[o].slot + threadIdx.x] = sum;
+            rec.partials[(size_t)blockIdx.x * (2 * kMaxObs) + 2 * ob.slot + threadIdx.x] = sum;
         }
         __syncthreads();
     }
@@ -1355,9 +1396,9 @@ __device__ __forceinline__ void cone_warm(const ConeArgs *__restrict__ a, uint64
 // register-window sweep, with many phase steps per pass (each restricted to the terms that
 // the host assigned to it, with its own workgroup row and tables) and separate tile-bit maps
 // for the load and the store.  L is the LDS element of the transposes (double: the half
-// buffer for complex128).  The workgroup row and the window table of a phase step are the
+// buffer for complex128; FEW: two full buffers).  The workgroup row and the window table of a phase step are the
 // same for every lane: the step reads them with scalar loads where it uses them.
-template <typename R, int T, int RB, typename L, bool REC = false>
+template <typename R, int T, int RB, typename L, bool REC = false, bool FEW = false>
 __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
                                            const ConeArgs *__restrict__ a, uint64_t tile, L *lds,
                                            const ConeRec *rec = nullptr, double *red = nullptr)
@@ -1376,7 +1417,15 @@ __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
     // the tile is complete (s_waitcnt vmcnt(0)): the first stage needs it anyway, and the
     // stage loop's waits then cover only the loads it issues itself
     __builtin_amdgcn_s_waitcnt(0x0F70);
-    int cur = a->load_win;
+    int cur = a->load_win, half = 0;
+    auto transpose = [&](int to) {
+        if constexpr (FEW) {
+            cone_transpose_next<RB>(x, lds + half, cur, to);
+            half = (1 << T) + (1 << T) / 16 - half;
+        } else {
+            cone_transpose<RB>(x, lds, cur, to);
+        }
+    };
     const int ns = a->n_stages;
     for (int s = 0; s < ns; ++s) {
         const uint32_t code = a->st[s];
@@ -1389,7 +1438,7 @@ __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
         gtab row = nullptr;
         if (has_phase) row = cone_thread_ends<RB>(a, code, th);
         if (w != cur) {
-            cone_transpose<RB>(x, lds, cur, w);
+            transpose(w);
             cur = w;
         }
         // butterflies, then (if any) the phase step, in one stage: fewer trips through the
@@ -1401,10 +1450,10 @@ __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
             const ctab wp = as_const(ph.wgf) + 2 * cone_row(ph, tile) * (T + 1);
             const double2 w0 = cmul(make_double2(ph.kre, ph.kim), ld2(wp, 0));
             const ctab qp = as_const(ph.dtab) + 2 * (1u << (T - RB)) * (1 + RB);
-            cone_diag<T, RB>(x, wp, w0, qp, th, ph.cmask, ph.xmask, row, w);
+            cone_diag<T, RB, FEW>(x, wp, w0, qp, th, ph.cmask, ph.xmask, row, w);
         }
     }
-    if (cur != a->store_win) cone_transpose<RB>(x, lds, cur, a->store_win);
+    if (cur != a->store_win) transpose(a->store_win);
     {
         const uint64_t gb = base | dep(thread_part<RB>(tid, a->store_win), a->store_runs, a->n_store_runs);
         if constexpr (REC) cone_record<R, RB>(x, gb, a->store_off, *rec, red);
@@ -1422,53 +1471,37 @@ __host__ __device__ constexpr size_t cone_tab_bytes(int n_phases)
     return (size_t)n_phases * ((T + 1) + (1 << RB)) * sizeof(double2);
 }
 
-// complex128 transposes through the half buffer; three waves per SIMD (at 128 registers,
-// which four would need, the compiler spills).  complex64 runs four workgroups per CU.
-template <int T, int RB>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(4)))
-void cone_c128_kernel(double2 *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
-                      int reverse)
+// complex128 transposes through the half buffer, so that four workgroups share a CU (four waves
+// per SIMD, as complex64 with its full buffer).  FEW: a launch of at most kConeFewTiles
+// workgroups leaves each CU one of them; its time is the latency of the chain of stages, which
+// two full buffers (one barrier per transpose instead of four) and all the registers shorten.
+// Measured with and without, complex128 N = 20: 170 and 188 us per fourth-order step; complex64
+// N = 19: 28.8 and 30.2 us per second-order step.
+template <typename R, bool FEW>
+using ConeLds = typename std::conditional<sizeof(R) == 8, typename std::conditional<FEW, double2, double>::type, float2>::type;
+template <typename R, int T, int RB, bool FEW>
+__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(FEW ? 1 : 4)))
+void cone_kernel(typename Vec<R>::T *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
+                 int reverse)
 {
-    constexpr int NE = 1 << T;
-    __shared__ double lds[NE + NE / 16];
+    constexpr int HB = (1 << T) + (1 << T) / 16;
+    __shared__ ConeLds<R, FEW> lds[FEW ? 2 * HB : HB];
     const uint64_t tile = reverse ? n_tiles - 1 - blockIdx.x : blockIdx.x;
-    cone_sweep<double, T, RB>(psi, a, tile, lds);
+    cone_sweep<R, T, RB, ConeLds<R, FEW>, false, FEW>(psi, a, tile, lds);
 }
 
-template <int T, int RB>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(4)))
-void cone_c64_kernel(float2 *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
-                     int reverse)
+// The last sweep of a vector's recorded segment, with the segment's observables (complex128:
+// three waves per SIMD, four would spill).
+template <typename R, int T, int RB, bool FEW>
+__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(FEW ? 1 : sizeof(R) == 8 ? 3 : 4)))
+void cone_rec_kernel(typename Vec<R>::T *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
+                     int reverse, ConeRec rec)
 {
-    constexpr int NE = 1 << T;
-    __shared__ float2 lds[NE + NE / 16];
-    const uint64_t tile = reverse ? n_tiles - 1 - blockIdx.x : blockIdx.x;
-    cone_sweep<float, T, RB>(psi, a, tile, lds);
-}
-
-// The last sweep of a vector's recorded segment, with the segment's observables.
-template <int T, int RB>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(4)))
-void cone_rec_c128_kernel(double2 *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
-                          int reverse, ConeRec rec)
-{
-    constexpr int NE = 1 << T;
-    __shared__ double lds[NE + NE / 16];
+    constexpr int HB = (1 << T) + (1 << T) / 16;
+    __shared__ ConeLds<R, FEW> lds[FEW ? 2 * HB : HB];
     __shared__ double red[2 << (T - RB - 6)];
     const uint64_t tile = reverse ? n_tiles - 1 - blockIdx.x : blockIdx.x;
-    cone_sweep<double, T, RB, double, true>(psi, a, tile, lds, &rec, red);
-}
-
-template <int T, int RB>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(4)))
-void cone_rec_c64_kernel(float2 *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
-                         int reverse, ConeRec rec)
-{
-    constexpr int NE = 1 << T;
-    __shared__ float2 lds[NE + NE / 16];
-    __shared__ double red[2 << (T - RB - 6)];
-    const uint64_t tile = reverse ? n_tiles - 1 - blockIdx.x : blockIdx.x;
-    cone_sweep<float, T, RB, float2, true>(psi, a, tile, lds, &rec, red);
+    cone_sweep<R, T, RB, ConeLds<R, FEW>, true, FEW>(psi, a, tile, lds, &rec, red);
 }
 
 // ------------------------------------------------------------ adjoint light-cone sweep
@@ -1936,6 +1969,24 @@ __device__ __forceinline__ void resident_phase(double2 p, int j, const double2 (
     }
 }
 
+// complex64: the factors of every amplitude, formed by the operations of the LDS sweep's phase
+// step.  A factor that differs in its last bit now and then rounds an amplitude to the other
+// FP32 neighbour, and later roundings spread that over the state; with one way to form
+// them complex64 states do not depend on the kernel.  Block (phase, chain), 256 threads.
+template <int T>
+__global__ __launch_bounds__(kThreads) void resident_diag_kernel(ResidentPhaseArgs a)
+{
+    __shared__ double2 qtab[1 << (T - kFixedBits)];
+    const ResidentPhase ph = a.phases[blockIdx.x];
+    const int ax = ph.d.axis >= 0 && ph.d.axis < 3 ? ph.d.axis : 0;
+    const double *wg = a.chains ? a.chains[blockIdx.y].wg[ax] : a.wg[ax];
+    const double *jt = a.chains ? a.chains[blockIdx.y].jt[ax] : a.jt[ax];
+    double2 *out = reinterpret_cast<double2 *>(a.tab) + (((size_t)blockIdx.y * a.n_phases + blockIdx.x) << a.n);
+    build_qtab<T>(qtab, ph.d, jt);
+    __syncthreads();
+    diag_factors<T>(1 << a.n, ph.d, wg, jt, qtab, (uint64_t)threadIdx.x, [&](int t, double2 z) { out[t] = z; });
+}
+
 // The factors of the phase tables, register-major: block = phase.
 template <int N>
 __global__ __launch_bounds__(resident_threads(N)) void resident_factor_kernel(const double *tab, double *fac)
@@ -2004,18 +2055,20 @@ __device__ void resident_record(const V (&x)[1 << RB], int w, V *lds, const ObsD
     resident_barrier<NT>();
 }
 
-// FAC: one system, alone on its CU: the phase steps multiply by factors formed once per plan,
+// SOLO: one system, alone on its CU: the phase steps multiply by factors formed once per plan,
 // loaded one op ahead, and the exchange buffer is double.  Otherwise (many chains) several
-// workgroups share a CU: the factors are formed from the small tables (a chain's factors
-// would take 64 KB per phase step at N = 12, more than the caches hold for 256 chains).
+// workgroups share a CU and complex128 forms the factors from the small tables (a chain's
+// factors take 64 KB per phase step at N = 12, more than the caches hold for 256 chains).
+// complex64 always multiplies by stored factors (resident_diag_kernel).
 template <typename R, int N, bool SOLO>
 __global__ __launch_bounds__(resident_threads(N)) void resident_kernel(ResidentArgs a)
 {
-    constexpr bool FAC = SOLO && N <= kResidentFactorSpins, FACL = FAC && N <= kResidentFactorLdsSpins;
+    constexpr bool ASC = resident_ascending(std::is_same<R, float>::value);
+    constexpr bool FAC = ASC || (SOLO && N <= kResidentFactorSpins), FACL = SOLO && FAC && N <= kResidentFactorLdsSpins;
+    constexpr bool AHEAD = N <= kResidentFactorSpins || !FAC;   // the next step's row fits the registers
     using V = typename Vec<R>::T;
     constexpr int RB = resident_reg_bits(N), NT = 1 << (N - RB), E = 1 << RB;
     constexpr int NW = (N + RB - 1) / RB, WT = N - RB;   // windows; start of the highest one
-    constexpr bool ASC = resident_ascending(std::is_same<R, float>::value);
     constexpr int HALF = (1 << N) + ((1 << N) >> 4) + 1;
     constexpr int B2 = SOLO && 2 * HALF * sizeof(V) <= 140 * 1024 ? HALF : 0;
     __shared__ V buf[HALF + B2];
@@ -2027,7 +2080,7 @@ __global__ __launch_bounds__(resident_threads(N)) void resident_kernel(ResidentA
     if (a.chains) {  // batched: one chain per workgroup
         psi = static_cast<V *>(a.chains[blockIdx.x].psi);
         rec = a.chains[blockIdx.x].rec;
-        tab += 2 * (size_t)blockIdx.x * a.n_phases * resident_phase_entries(N);
+        tab += 2 * (size_t)blockIdx.x * a.n_phases * (ASC ? 1 << N : resident_phase_entries(N));
     } else {
         psi = reinterpret_cast<V *>(a.psi[blockIdx.x]);
     }
@@ -2038,14 +2091,15 @@ __global__ __launch_bounds__(resident_threads(N)) void resident_kernel(ResidentA
     bool top = true;   // the register window: the highest or the lowest
     // the next phase step's factors, or the thread's row of its table, loaded one op ahead
     extern __shared__ double2 resident_dyn[];
+    const double2 *fac = reinterpret_cast<const double2 *>(ASC ? tab : a.fac);
     if constexpr (FACL) {
-        const double2 *f = reinterpret_cast<const double2 *>(a.fac);
+        const double2 *f = fac;
         for (int i = tid; i < a.n_phases << N; i += NT) resident_dyn[i] = f[i];   // each thread reads what it wrote
     }
     double2 th[FAC ? E : 1 + RB];
     auto load_row = [&](int phase) {
         const double2 *t = FACL  ? resident_dyn + ((size_t)phase << N)
-                           : FAC ? reinterpret_cast<const double2 *>(a.fac) + ((size_t)phase << N)
+                           : FAC ? fac + ((size_t)phase << N)
                                  : reinterpret_cast<const double2 *>(tab) + (size_t)phase * resident_phase_entries(N);
 #pragma unroll
         for (int v = 0; v < (FAC ? E : 1 + RB); ++v) th[v] = t[v * NT + tid];
@@ -2063,7 +2117,7 @@ __global__ __launch_bounds__(resident_threads(N)) void resident_kernel(ResidentA
         op1 = op_at(0);
         op2 = op_at(1);
     }
-    load_row(op1.phase >= 0 ? op1.phase : 0);
+    if constexpr (AHEAD) load_row(op1.phase >= 0 ? op1.phase : 0);
     if (a.rec_first) resident_record<N, RB>(x, WT, buf, a.obs, a.n_obs, a.rec_rows - a.slots);
     for (int r = 0; r < reps; ++r) {
         for (int s = 0; s < a.n_ops; ++s) {
@@ -2077,7 +2131,10 @@ __global__ __launch_bounds__(resident_threads(N)) void resident_kernel(ResidentA
                 }
             }
             if (op.phase >= 0) {
-                if constexpr (FAC) {
+                if constexpr (!AHEAD) {
+#pragma unroll
+                    for (int j = 0; j < E; ++j) apply_phase(x[j], fac[((size_t)op.phase << N) + j * NT + tid]);
+                } else if constexpr (FAC) {
 #pragma unroll
                     for (int j = 0; j < E; ++j) apply_phase(x[j], th[j]);
                 } else {
@@ -2086,7 +2143,9 @@ __global__ __launch_bounds__(resident_threads(N)) void resident_kernel(ResidentA
                     resident_phase<RB, RB>(th[0], 0, th, q, [&](int j, double2 z) { apply_phase(x[j], z); });
                 }
             }
-            if (op1.phase >= 0) load_row(op1.phase);
+            if constexpr (AHEAD) {
+                if (op1.phase >= 0) load_row(op1.phase);
+            }
             if (op.post) {
                 if constexpr (NW == 1) {
                     resident_layer<N, RB, 0, false>(x, lds);
@@ -2834,7 +2893,7 @@ template <typename R, int N>
 static hipError_t launch_res_n(const ResidentArgs &a, int nvec, hipStream_t s)
 {
     const size_t dyn = N <= kResidentFactorLdsSpins ? ((size_t)a.n_phases << N) * sizeof(double2) : 0;
-    if (!a.chains && (a.fac || N > kResidentFactorSpins) && dyn <= 48 * 1024) {
+    if (!a.chains && (a.fac || sizeof(R) == 4 || N > kResidentFactorSpins) && dyn <= 48 * 1024) {
         hipLaunchKernelGGL((resident_kernel<R, N, true>), dim3(nvec), dim3(resident_threads(N)), dyn, s, a);
         return hipGetLastError();
     }
@@ -2870,13 +2929,32 @@ hipError_t launch_resident(int dtype, const ResidentArgs &a, int nvec, hipStream
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_resident_phases(const ResidentPhaseArgs &a, int nchains, hipStream_t s)
+hipError_t launch_resident_phases(int dtype, const ResidentPhaseArgs &a, int nchains, hipStream_t s)
 {
     if (a.n < 1 || a.n > 14 || a.n_phases <= 0 || !a.phases || !a.tab || (nchains > 0) != (a.chains != nullptr))
         return hipErrorInvalidValue;
-    const int nt = resident_threads(a.n) > 16 ? resident_threads(a.n) : 16;
-    hipLaunchKernelGGL(resident_phase_kernel, dim3(a.n_phases, nchains > 0 ? nchains : 1), dim3(nt), 0, s, a);
-    return hipGetLastError();
+    const dim3 grid(a.n_phases, nchains > 0 ? nchains : 1);
+    if (!resident_ascending(dtype)) {
+        const int nt = resident_threads(a.n) > 16 ? resident_threads(a.n) : 16;
+        hipLaunchKernelGGL(resident_phase_kernel, grid, dim3(nt), 0, s, a);
+        return hipGetLastError();
+    }
+#define TS_RESD_CASE(TT)                                                                       \
+    case TT:                                                                                   \
+        hipLaunchKernelGGL((resident_diag_kernel<TT>), grid, dim3(kThreads), 0, s, a);         \
+        return hipGetLastError();
+    switch (a.n < 8 ? 8 : a.n) {
+        TS_RESD_CASE(8)
+        TS_RESD_CASE(9)
+        TS_RESD_CASE(10)
+        TS_RESD_CASE(11)
+        TS_RESD_CASE(12)
+        TS_RESD_CASE(13)
+        TS_RESD_CASE(14)
+    default: break;
+    }
+#undef TS_RESD_CASE
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_resident_factors(int n, int n_phases, const double *tab, double *fac, hipStream_t s)
@@ -3032,49 +3110,51 @@ hipError_t launch_sweep_pair(int dtype, int T, int RB, void *psi, void *lam, con
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_cone(int dtype, int T, int RB, void *psi, const ConeArgs *a, int n_phases,
-                       uint64_t n_tiles, int reverse, hipStream_t s)
+template <typename R, int T>
+static hipError_t launch_cone_t(typename Vec<R>::T *psi, const ConeArgs *a, uint64_t n_tiles, int reverse,
+                                const ConeRec *rec, hipStream_t s)
+{
+    const dim3 grid((uint32_t)n_tiles), block(1 << (T - 4));
+    if (n_tiles <= kConeFewTiles) {
+        if (rec)
+            hipLaunchKernelGGL((cone_rec_kernel<R, T, 4, true>), grid, block, 0, s, psi, a, n_tiles, reverse, *rec);
+        else
+            hipLaunchKernelGGL((cone_kernel<R, T, 4, true>), grid, block, 0, s, psi, a, n_tiles, reverse);
+        return hipGetLastError();
+    }
+    if (rec)
+        hipLaunchKernelGGL((cone_rec_kernel<R, T, 4, false>), grid, block, 0, s, psi, a, n_tiles, reverse, *rec);
+    else
+        hipLaunchKernelGGL((cone_kernel<R, T, 4, false>), grid, block, 0, s, psi, a, n_tiles, reverse);
+    return hipGetLastError();
+}
+
+static hipError_t launch_cone_any(int dtype, int T, int RB, void *psi, const ConeArgs *a, int n_phases,
+                                  uint64_t n_tiles, int reverse, const ConeRec *rec, hipStream_t s)
 {
     if (!a || RB != 4 || n_phases < 0 || n_phases > kConePhases || n_tiles == 0 || n_tiles > 0x7fffffffull)
         return hipErrorInvalidValue;
-#define TS_CONE_CASE(TT)                                                                          \
-    if (T == TT) {                                                                                \
-        if (dtype == 0)                                                                           \
-            hipLaunchKernelGGL((cone_c128_kernel<TT, 4>), dim3((uint32_t)n_tiles), dim3(1 << (TT - 4)), \
-                               0, s, static_cast<double2 *>(psi), a, n_tiles, reverse);        \
-        else                                                                                      \
-            hipLaunchKernelGGL((cone_c64_kernel<TT, 4>), dim3((uint32_t)n_tiles), dim3(1 << (TT - 4)), \
-                               0, s, static_cast<float2 *>(psi), a, n_tiles, reverse);         \
-        return hipGetLastError();                                                                 \
-    }
+#define TS_CONE_CASE(TT)                                                                              \
+    if (T == TT)                                                                                      \
+        return dtype == 0 ? launch_cone_t<double, TT>(static_cast<double2 *>(psi), a, n_tiles, reverse, rec, s) \
+                          : launch_cone_t<float, TT>(static_cast<float2 *>(psi), a, n_tiles, reverse, rec, s);
     TS_CONE_CASE(11)
     TS_CONE_CASE(12)
 #undef TS_CONE_CASE
     return hipErrorInvalidValue;
 }
 
+hipError_t launch_cone(int dtype, int T, int RB, void *psi, const ConeArgs *a, int n_phases,
+                       uint64_t n_tiles, int reverse, hipStream_t s)
+{
+    return launch_cone_any(dtype, T, RB, psi, a, n_phases, n_tiles, reverse, nullptr, s);
+}
+
 hipError_t launch_cone_rec(int dtype, int T, int RB, void *psi, const ConeArgs *a, int n_phases,
                            uint64_t n_tiles, int reverse, const ConeRec &rec, hipStream_t s)
 {
-    if (!a || !rec.partials || RB != 4 || n_phases < 0 || n_phases > kConePhases || n_tiles == 0 ||
-        n_tiles > 0x7fffffffull || rec.n_obs < 0 || rec.n_obs > kConeRecMax)
-        return hipErrorInvalidValue;
-#define TS_CONER_CASE(TT)                                                                         \
-    if (T == TT) {                                                                                \
-        if (dtype == 0)                                                                           \
-            hipLaunchKernelGGL((cone_rec_c128_kernel<TT, 4>), dim3((uint32_t)n_tiles),             \
-                               dim3(1 << (TT - 4)), 0, s, static_cast<double2 *>(psi), a, n_tiles, \
-                               reverse, rec);                                                     \
-        else                                                                                      \
-            hipLaunchKernelGGL((cone_rec_c64_kernel<TT, 4>), dim3((uint32_t)n_tiles),              \
-                               dim3(1 << (TT - 4)), 0, s, static_cast<float2 *>(psi), a, n_tiles,  \
-                               reverse, rec);                                                     \
-        return hipGetLastError();                                                                 \
-    }
-    TS_CONER_CASE(11)
-    TS_CONER_CASE(12)
-#undef TS_CONER_CASE
-    return hipErrorInvalidValue;
+    if (!rec.partials || rec.n_obs < 0 || rec.n_obs > kConeRecMax) return hipErrorInvalidValue;
+    return launch_cone_any(dtype, T, RB, psi, a, n_phases, n_tiles, reverse, &rec, s);
 }
 
 hipError_t launch_cone_pair(int dtype, int T, int RB, void *psi, void *lam, const ConeArgs *a, int n_phases,

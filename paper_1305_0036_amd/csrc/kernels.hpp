@@ -221,11 +221,13 @@ struct ResidentArgs {
     const ResidentOp *ops;
     int32_t n_ops;
     int32_t n;            // spins
-    // phase tables [n_phases][resident_phase_entries(n)] of (re, im) pairs, from
-    // launch_resident_phases; batched: chain c's tables start at phase c * n_phases
+    // phase tables [n_phases][resident_phase_entries(n)] of (re, im) pairs (complex64: factors
+    // [n_phases][2^n]), from launch_resident_phases; batched: chain c's tables start at phase
+    // c * n_phases
     const double *tab;
-    // non-NULL (not batched): every phase step's factors [n_phases][2^n] (register-major, as the
-    // threads hold the amplitudes), from launch_resident_factors
+    // complex128, not batched, n <= kResidentFactorSpins: every phase step's factors
+    // [n_phases][2^n] (register-major, as the threads hold the amplitudes), from
+    // launch_resident_factors
     const double *fac;
     const ResidentChain *chains;  // batched: per-workgroup state, energies and records
     int32_t n_phases;
@@ -408,6 +410,10 @@ hipError_t launch_cone_pair(int dtype, int T, int RB, void *psi, void *lam, cons
                             const ConeGradArgs *g, int n_slots, double *slots, int stride, uint64_t n_tiles,
                             int reverse, hipStream_t s);
 
+// Launches of at most this many workgroups (one per CU) run the light-cone kernel with two full
+// transpose buffers (139 KB at 2^12 complex128 amplitudes), larger ones the one of four waves
+// per SIMD.
+constexpr uint64_t kConeFewTiles = 256;
 // One light-cone sweep of n_tiles workgroups; `a` points to device memory and n_phases is its
 // n_phases (checked against the limit).  The phase tables that `a` names are read-only while
 // the sweep runs (the kernel reads them through the scalar data cache).
@@ -432,8 +438,9 @@ hipError_t launch_sweep(int dtype, int T, void *psi, const SweepArgs &a, uint32_
                         hipStream_t s);
 hipError_t launch_sweep_reg(int dtype, int T, int RB, void *psi, const RegSweepArgs &a, hipStream_t s);
 hipError_t launch_resident(int dtype, const ResidentArgs &a, int nvec, hipStream_t s);
-// Fills the phase tables of one system (nchains = 0) or of every chain.
-hipError_t launch_resident_phases(const ResidentPhaseArgs &a, int nchains, hipStream_t s);
+// Fills the phase tables of one system (nchains = 0) or of every chain; complex64: the factors
+// [n_phases][2^n] themselves.
+hipError_t launch_resident_phases(int dtype, const ResidentPhaseArgs &a, int nchains, hipStream_t s);
 // The factors of one system's phase tables `tab`.
 hipError_t launch_resident_factors(int n, int n_phases, const double *tab, double *fac, hipStream_t s);
 // Sums of the observables per workgroup into partials [nblocks][2 * kMaxObs]; launch_finalize

@@ -1391,9 +1391,10 @@ ts_status resident_args(ts_ctx *c, PlanEntry *pe, int dtype, tsk::ResidentArgs *
         st = alloc(pe->resident_phases, phases.size() * sizeof(tsk::ResidentPhase));
         if (st != TS_OK) return st;
         DevBuf tab;
-        st = alloc(tab, phases.size() * tsk::resident_phase_entries(n) * sizeof(double2));
+        const bool asc = tsk::resident_ascending(dtype);   // the tables are the factors
+        st = alloc(tab, phases.size() * (asc ? (size_t)1 << n : tsk::resident_phase_entries(n)) * sizeof(double2));
         if (st != TS_OK) return st;
-        const bool fac = n <= tsk::kResidentFactorSpins;
+        const bool fac = !asc && n <= tsk::kResidentFactorSpins;
         if (fac) st = alloc(pe->resident_fac, (phases.size() << n) * sizeof(double2));
         if (st != TS_OK) return st;
         TS_HIP(hipMemcpy(pe->resident_ops.p, ops.data(), ops.size() * sizeof(tsk::ResidentOp),
@@ -1404,7 +1405,7 @@ ts_status resident_args(ts_ctx *c, PlanEntry *pe, int dtype, tsk::ResidentArgs *
         pa.n_phases = (int)phases.size();
         pa.n = n;
         pa.tab = static_cast<double *>(tab.p);
-        TS_HIP(tsk::launch_resident_phases(pa, 0, nullptr));
+        TS_HIP(tsk::launch_resident_phases(dtype, pa, 0, nullptr));
         if (fac) TS_HIP(tsk::launch_resident_factors(n, pa.n_phases, pa.tab, static_cast<double *>(pe->resident_fac.p), nullptr));
         TS_HIP(hipStreamSynchronize(nullptr));  // the tables are read on any stream
         pe->resident_n_ops = (int)ops.size();
@@ -2003,7 +2004,7 @@ hipError_t run_launch(int dtype, const BatchLaunch &L, hipStream_t s)
 {
     switch (L.kind) {
     case 0: return tsk::launch_resident(dtype, L.ra, (int)L.count, s);
-    case 4: return tsk::launch_resident_phases(L.pa, (int)L.count, s);
+    case 4: return tsk::launch_resident_phases(dtype, L.pa, (int)L.count, s);
     case 1: return tsk::launch_sweep_reg_batch(dtype, L.T, L.RB, L.sa, L.count, s);
     case 3:
         return tsk::launch_cone_batch(dtype, L.T, L.RB, L.cone_packed, L.cone_off, L.cone_args, L.count, L.tiles,
@@ -2081,10 +2082,11 @@ ts_status build_batch_program(ts_ctx *ctx, char *psi_packed, const int64_t *psi_
                 rc.push_back(x);
             }
             // The phase tables of a class of many chains outgrow its states (about 60 KB per
-            // chain at 10 spins, 250 KB at 12): at most kResidentTabBytes of them are kept.
+            // chain at 10 spins, 250 KB at 12; complex64 600 KB): at most kResidentTabBytes of them are kept.
             // A class that fits has them filled once, here; a larger one runs in groups of
             // chains that share the buffer, each filling it anew.
-            const size_t per_chain = phases.size() * tsk::resident_phase_entries(n) * sizeof(double2);
+            const size_t per_chain = phases.size() * sizeof(double2) *
+                                     (tsk::resident_ascending(dtype) ? (size_t)1 << n : tsk::resident_phase_entries(n));
             const size_t group = std::min<size_t>(mem.size(),
                                                   std::min<size_t>(65535, std::max<size_t>(1, kResidentTabBytes / per_chain)));
             auto tb = std::make_unique<DevBuf>();
@@ -2114,7 +2116,7 @@ ts_status build_batch_program(ts_ctx *ctx, char *psi_packed, const int64_t *psi_
                 if (group < mem.size())
                     L.push_back(fill);
                 else
-                    TS_HIP(tsk::launch_resident_phases(fill.pa, (int)fill.count, nullptr));
+                    TS_HIP(tsk::launch_resident_phases(dtype, fill.pa, (int)fill.count, nullptr));
                 L.push_back(bl);
             }
             TS_HIP(hipStreamSynchronize(nullptr));

@@ -45,7 +45,7 @@ def is_c128_sweep(name: str) -> bool:
     """A complex128 sweep dispatch: the light-cone kernel, the register-window kernels on
     doubles, or the half-LDS kernel (complex128 only) of the ping-pong sweeps on the top bit
     group."""
-    return ("cone_c128_kernel" in name or "sweep_half_kernel" in name or
+    return ("cone_kernel<double" in name or "sweep_half_kernel" in name or
             (("sweep_reg_kernel" in name or "sweep_pipe_kernel" in name) and "double" in name))
 
 
