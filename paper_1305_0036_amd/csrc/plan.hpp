@@ -173,11 +173,11 @@ struct ConePlan {
 // Light-cone plan of a folded chain for n spins, tiles of T bits of which the s lowest
 // memory bits are in every tile, bonds (i, j) as listed (duplicates allowed).  max_adv
 // bounds the layers one spin takes in one sweep and max_phases the phase steps of one sweep
-// (<= 0: no bound).  Returns false (and
+// (<= 0: no bound); even spreads the windows evenly.  Returns false (and
 // leaves `out` unspecified) when the windows cannot cover the spins under these rules:
 // n <= T, s >= T, or a plan longer than max_sweeps.
 bool make_cone_plan(const FoldedChain &fc, int n, int T, int s,
                     const std::vector<std::pair<int, int>> &bonds, int max_adv, size_t max_sweeps,
-                    ConePlan &out, int max_phases = 0);
+                    ConePlan &out, int max_phases = 0, bool even = false);
 
 }  // namespace ts

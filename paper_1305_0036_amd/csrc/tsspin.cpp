@@ -332,6 +332,10 @@ double pingpong_sweep_us(int dtype, int T)
 bool cone_stages(const ts::ConeSweep &sw, int T, int RB, int s, tsk::ConeArgs &a,
                  std::vector<int> &phase_win, int *transposes);
 
+// Light-cone windows spread evenly (fewer sweeps).  complex64 keeps the windows packed from the
+// left: its roundings depend on which sweep takes which layer, and its results stay what they were.
+bool even_windows(int dtype) { return dtype == TS_C128; }
+
 bool cone_candidate(ts_ctx *c, PlanEntry *pe, int T, int dtype, int mode)
 {
     std::vector<std::pair<int, int>> bonds;
@@ -339,7 +343,7 @@ bool cone_candidate(ts_ctx *c, PlanEntry *pe, int T, int dtype, int mode)
     ts::ConePlan cp;
     const size_t limit = 4 * pe->plan.sweeps.size() + 16;
     if (!ts::make_cone_plan(pe->plan.chain, c->n, T, kConeLowBits, bonds, c->cone_adv, limit, cp,
-                            tsk::kConePhases))
+                            tsk::kConePhases, even_windows(dtype)))
         return false;
     double cost = 0.0;
     for (const ts::ConeSweep &sw : cp.sweeps) {
@@ -410,17 +414,50 @@ ts_status build_plan(ts_ctx *c, int dtype, int T, int order, double dt, int64_t 
     return TS_OK;
 }
 
+// Narrow tiles: complex128 states of at most kNarrowSpins spins, neither tuned nor configured,
+// leave most CUs idle at the default width (2^(n - 12) workgroups, at most 128 up to n = 19), and
+// a sweep is the latency of one workgroup.  See resolve_tile for the widths and what they measured.
+// complex64 keeps the default: its roundings depend on the tiles, and its results stay what
+// they were.
+constexpr int kNarrowSpins = 19;
+bool narrow_tiles(const ts_ctx *c, int dtype)
+{
+    return dtype == TS_C128 && c->tile_bits[dtype] == 0 && c->reg_bits[dtype] == 4 && c->sweep_variant[dtype] == 4 &&
+           c->n > default_tile_bits(dtype) && c->n <= kNarrowSpins;
+}
+// Amplitudes per thread (2^RB) of the ping-pong sweeps at width T: narrow tiles halve them, which
+// gives the SIMDs of a CU twice the waves.
+int sweep_reg_bits(const ts_ctx *c, int dtype, int T)
+{
+    return narrow_tiles(c, dtype) && T < default_tile_bits(dtype) ? 3 : c->reg_bits[dtype];
+}
+
 // Tile width of ts_evolve when the caller fixed none.  The default (12) keeps every tile
 // wide enough for runs of >= 128 bytes and lets several workgroups share a CU; a wider
 // tile is taken when it cuts the bit groups of the ping-pong sweeps (one sweep fewer per
 // layer for each group saved: the 5 x 6 dipolar lattice in complex64 needs 4 groups at 12
 // and 3 at 13, 61 instead of 41 sweeps per step), unless the light-cone form, which runs at
 // the default width, is faster by the cost model than the wider ping-pong plan.
+//
+// Where narrow tiles are allowed (complex128, 13 to 19 spins; us per fourth-order step, 16
+// steps a call): ping-pong plans take the narrowest tile that still needs two bit groups,
+// ceil((n + 3) / 2), with half the amplitudes per thread.  Ring, default width against narrow:
+// 203 / 132 at n = 14, 213 / 151 at 16, 239 / 171 at 17, 270 / 219 at 19 (at 20 the default's
+// 311 stand against 445 at width 11).  At 13 one workgroup that holds the whole state is faster
+// still (111; width 9 131, default 197).  Light-cone plans keep the default width, as the same
+// chain in a batch does (width 11 measured 5 to 10% less up to n = 18, 5% more at 19).
 ts_status resolve_tile(ts_ctx *c, int dtype, int order, double dt, int64_t nsteps, int *T_out)
 {
     const int T0 = c->tile_bits[dtype] > 0 ? c->tile_bits[dtype] : default_tile_bits(dtype);
     *T_out = T0;
     if (c->tile_bits[dtype] > 0 || c->n <= T0) return TS_OK;
+    if (narrow_tiles(c, dtype)) {
+        PlanEntry *p0;
+        ts_status st = build_plan(c, dtype, T0, order, dt, nsteps, &p0);
+        if (st != TS_OK) return st;
+        if (!p0->cone) *T_out = c->n == T0 + 1 ? c->n : (c->n + min_run_bits(dtype) + 1) / 2;
+        return TS_OK;
+    }
     auto ngroups = [&](int T) {
         std::vector<uint64_t> g, t;
         ts::plan_groups(c->n, T, min_run_bits(dtype), g, t);
@@ -697,11 +734,11 @@ constexpr size_t kTileRotBytes = (size_t)4 << 30;
 // Launch arguments of every sweep of a tiled plan, built once per plan (tables included).
 ts_status prepare_sweeps(ts_ctx *c, PlanEntry *pe, int dtype)
 {
-    if (pe->prepared && pe->reg_bits == c->reg_bits[dtype]) return TS_OK;
     const ts::Plan &P = pe->plan;
     const int n = c->n;
     const int T = P.tile_bits;
-    const int RB = c->reg_bits[dtype];
+    const int RB = sweep_reg_bits(c, dtype, T);
+    if (pe->prepared && pe->reg_bits == RB) return TS_OK;
     const uint64_t all = (1ull << n) - 1;
     pe->lds_args.clear();
     pe->reg_args.clear();
@@ -2652,7 +2689,7 @@ ts_status ts_plan_describe(ts_ctx *ctx, ts_dtype dtype, double dt, int64_t nstep
     }
     *n_sweeps = (int64_t)P.sweeps.size();
     if (!out) return TS_OK;
-    const int RB = ctx->reg_bits[dtype];
+    const int RB = tile_bits > 0 ? ctx->reg_bits[dtype] : sweep_reg_bits(ctx, dtype, T);
     for (int64_t k = 0; k < *n_sweeps && k < cap; ++k) {
         const ts::Sweep &s = P.sweeps[k];
         int64_t *r = out + 16 * k;
@@ -2727,7 +2764,8 @@ ts_status ts_cone_describe(ts_ctx *ctx, ts_dtype dtype, double dt, int64_t nstep
     }
     std::vector<std::pair<int, int>> bonds;
     for (size_t k = 0; k < ctx->bi.size(); ++k) bonds.push_back({ctx->bi[k], ctx->bj[k]});
-    if (!ts::make_cone_plan(P.chain, ctx->n, T, s, bonds, max_adv, 1u << 20, cp, tsk::kConePhases))
+    if (!ts::make_cone_plan(P.chain, ctx->n, T, s, bonds, max_adv, 1u << 20, cp, tsk::kConePhases,
+                           even_windows(dtype)))
         return fail(TS_EINVAL, "no light-cone plan for these sizes");
     if (used) {
         *used = 0;
@@ -3126,7 +3164,10 @@ extern "C" ts_status ts_get_kernel_config(ts_ctx *ctx, ts_dtype dtype, int32_t o
     ts_status st = resolve_tile(ctx, dtype, order, 1.0, 1, &T);   // the plan's shape does not depend on dt
     if (st != TS_OK) return st;
     *tile_bits = T;
-    *reg_bits = ctx->reg_bits[dtype];
+    PlanEntry *pe;
+    st = build_plan(ctx, dtype, T, order, 1.0, 1, &pe);
+    if (st != TS_OK) return st;
+    *reg_bits = pe->cone ? 4 : sweep_reg_bits(ctx, dtype, T);
     *variant = ctx->sweep_variant[dtype];
     return TS_OK;
 }
