@@ -390,7 +390,12 @@ ts_status build_plan(ts_ctx *c, int dtype, int T, int order, double dt, int64_t 
 {
     uint64_t dtb;
     std::memcpy(&dtb, &dt, sizeof dtb);
-    auto key = std::make_tuple(dtype + (adjoint ? (split ? 2 : 4) : 0), T, order, dtb, nsteps);
+    // the light-cone form depends on the context's kernel configuration, which tuning changes: a
+    // plan made under another one is another plan
+    const int cm = adjoint || c->reg_bits[dtype] != 4 || (T != 11 && T != 12) ? 0
+                   : c->cone_mode >= 0                                        ? c->cone_mode
+                                                                              : c->sweep_variant[dtype] == 4;
+    auto key = std::make_tuple(dtype + (adjoint ? (split ? 2 : 4) : 0) + 8 * cm, T, order, dtb, nsteps);
     auto it = c->plans.find(key);
     if (it != c->plans.end()) {
         *out = it->second.get();
@@ -406,9 +411,7 @@ ts_status build_plan(ts_ctx *c, int dtype, int T, int order, double dt, int64_t 
         return fail(TS_EINVAL, std::string("plan: ") + e.what());
     }
     for (const auto &d : pe->plan.chain.diags) pe->diag_args.push_back(diag_args(d));
-    const int cm = c->cone_mode >= 0 ? c->cone_mode : (c->sweep_variant[dtype] == 4 ? 1 : 0);
-    if (!adjoint && cm > 0 && !pe->plan.resident && c->reg_bits[dtype] == 4 && (T == 11 || T == 12))
-        pe->cone = cone_candidate(c, pe.get(), T, dtype, cm);
+    if (cm > 0 && !pe->plan.resident) pe->cone = cone_candidate(c, pe.get(), T, dtype, cm);
     *out = pe.get();
     c->plans.emplace(key, std::move(pe));
     return TS_OK;

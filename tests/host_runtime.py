@@ -1,0 +1,108 @@
+"""The library on a host-only HIP runtime (hip_host.cpp): `python tests/host_runtime.py <stub.so>
+<name>` runs one check below and prints its result as JSON.  A process of its own, without torch,
+because the stand-in has to be loaded before any HIP runtime."""
+from __future__ import annotations
+
+import ctypes as C
+import json
+import os
+import subprocess
+import sys
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LIB = os.path.join(ROOT, "paper_1305_0036_amd", "libtsspin.so")
+C128, C64 = 0, 1
+
+
+def run(tmp_path, check, *args, env=None):
+    """Run `check(*args)` in a process with the stand-in preloaded and return its result."""
+    so = os.path.join(str(tmp_path), "hip_host.so")
+    if not os.path.exists(so):
+        subprocess.run(["g++", "-O1", "-shared", "-fPIC", "-I/opt/rocm/include", "-o", so,
+                        os.path.join(ROOT, "tests", "hip_host.cpp")], check=True)
+    e = dict(os.environ, LD_PRELOAD=so, TSSPIN_NO_TUNE_CACHE="1", **(env or {}))
+    p = subprocess.run([sys.executable, os.path.abspath(__file__), check, json.dumps(args)], env=e,
+                       capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stderr[-2000:]
+    return json.loads(p.stdout.splitlines()[-1])
+
+
+class Bond(C.Structure):
+    _fields_ = [("i", C.c_int32), ("j", C.c_int32), ("jx", C.c_double), ("jy", C.c_double), ("jz", C.c_double)]
+
+
+class Host:
+    def __init__(self):
+        self.lib = C.CDLL(LIB)
+        self.rt = C.CDLL(os.environ["LD_PRELOAD"])
+        for f in ("host_held", "host_peak"):
+            getattr(self.rt, f).restype = C.c_size_t
+        self.lib.ts_last_error.restype = C.c_char_p
+
+    def ok(self, rc):
+        assert rc == 0, (rc, self.lib.ts_last_error())
+
+    @staticmethod
+    def bonds(n, ring=False):
+        b = [(i, i + 1, 0.7 + 0.01 * i, 0.8, 0.9) for i in range(n - 1)] + ([(0, n - 1, 0.5, 0.6, 0.7)] if ring else [])
+        return (Bond * max(1, len(b)))(*b), len(b)
+
+    def system(self, n, ring=False):
+        b, nb = self.bonds(n, ring)
+        f = (C.c_double * (3 * n))(*[0.1 + 0.01 * i for i in range(3 * n)])
+        ctx = C.c_void_p()
+        self.ok(self.lib.ts_create(n, b, nb, f, C.byref(ctx)))
+        return ctx
+
+    def evolve(self, ctx, dtype, steps, order=4, dt=0.05):
+        psi = (C.c_void_p * 1)(4096)   # never dereferenced: the kernels do nothing
+        self.ok(self.lib.ts_evolve(ctx, psi, 1, dtype, C.c_double(dt), C.c_int64(steps), order, None, 0, 1, None, None))
+
+    def batch(self, ns):
+        b, off, f = [], [0], []
+        for n in ns:
+            x, nb = self.bonds(n)
+            b += list(x)[:nb]
+            off.append(len(b))
+            f += [0.1 + 0.01 * i for i in range(3 * n)]
+        ctx = C.c_void_p()
+        self.ok(self.lib.ts_create_batch(len(ns), (C.c_int32 * len(ns))(*ns), (Bond * max(1, len(b)))(*b),
+                                         (C.c_int32 * len(off))(*off), (C.c_double * len(f))(*f), C.byref(ctx)))
+        return ctx
+
+    def evolve_batch(self, ctx, ns, dtype, steps, order=4, dt=0.05, at=4096):
+        off, t = [], 0
+        for n in ns:
+            off.append(t)
+            t += 1 << n
+        return self.lib.ts_evolve_batch(ctx, C.c_void_p(at), (C.c_int64 * len(off))(*off), dtype, C.c_double(dt),
+                                        C.c_int64(steps), order, None, 0, 1, None, None)
+
+    def autotune(self, ctx, dtype, use_cache, order=4):
+        ms = C.c_double()
+        self.ok(self.lib.ts_autotune(ctx, dtype, order, C.c_void_p(4096), use_cache, C.byref(ms), None))
+
+    def launches(self, part):
+        return self.rt.host_launches(part.encode())
+
+
+# ---------------------------------------------------------------- checks
+
+def tuned_after_evolving(h, dtype):
+    ctx = h.system(20)
+    h.evolve(ctx, dtype, 2)
+    before = h.launches("cone_kernel")
+    h.autotune(ctx, dtype, 1)
+    h.rt.host_reset()
+    h.evolve(ctx, dtype, 2)
+    return {"before": before, "after_cone": h.launches("cone_kernel"), "after_reg": h.launches("sweep_reg_kernel")}
+
+
+def tuner_launches(h, dtype):
+    ctx = h.system(20)
+    h.autotune(ctx, dtype, 0)
+    return {"cone": h.launches("cone_kernel")}
+
+
+if __name__ == "__main__":
+    print(json.dumps(globals()[sys.argv[1]](Host(), *json.loads(sys.argv[2]))))
