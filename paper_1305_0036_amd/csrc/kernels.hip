@@ -939,6 +939,15 @@ __device__ __forceinline__ void cone_transpose(V (&x)[1 << RB], V *lds, int from
     for (int r = 0; r < (1 << RB); ++r) x[r] = pt[r * mt];
 }
 
+// Elements of a transpose buffer, and whether two full ones leave room for a second workgroup on
+// the CU (160 KB).
+__host__ __device__ constexpr int cone_buffer(int T) { return (1 << T) + (1 << T) / 16; }
+template <int T, typename L>
+__host__ __device__ constexpr bool cone_two_buffers()
+{
+    return 2 * cone_buffer(T) * sizeof(L) <= 80 * 1024 - 1024;
+}
+
 // The same through two full buffers in turn (`lds`: the one that the transpose before did not
 // use): the barrier between has seen every wave past its reads of it, so one barrier is enough.
 template <int RB, typename V>
@@ -1396,8 +1405,8 @@ __device__ __forceinline__ void cone_warm(const ConeArgs *__restrict__ a, uint64
 // register-window sweep, with many phase steps per pass (each restricted to the terms that
 // the host assigned to it, with its own workgroup row and tables) and separate tile-bit maps
 // for the load and the store.  L is the LDS element of the transposes (double: the half
-// buffer for complex128; FEW: two full buffers).  The workgroup row and the window table of a phase step are the
-// same for every lane: the step reads them with scalar loads where it uses them.
+// buffer for complex128; FEW: a full buffer, or two).  The workgroup row and the window table of a
+// phase step are the same for every lane: the step reads them with scalar loads where it uses them.
 template <typename R, int T, int RB, typename L, bool REC = false, bool FEW = false>
 __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
                                            const ConeArgs *__restrict__ a, uint64_t tile, L *lds,
@@ -1419,9 +1428,9 @@ __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
     __builtin_amdgcn_s_waitcnt(0x0F70);
     int cur = a->load_win, half = 0;
     auto transpose = [&](int to) {
-        if constexpr (FEW) {
+        if constexpr (FEW && cone_two_buffers<T, L>()) {
             cone_transpose_next<RB>(x, lds + half, cur, to);
-            half = (1 << T) + (1 << T) / 16 - half;
+            half = cone_buffer(T) - half;
         } else {
             cone_transpose<RB>(x, lds, cur, to);
         }
@@ -1473,19 +1482,28 @@ __host__ __device__ constexpr size_t cone_tab_bytes(int n_phases)
 
 // complex128 transposes through the half buffer, so that four workgroups share a CU (four waves
 // per SIMD, as complex64 with its full buffer).  FEW: a launch of at most kConeFewTiles
-// workgroups leaves each CU one of them; its time is the latency of the chain of stages, which
-// two full buffers (one barrier per transpose instead of four) and all the registers shorten.
-// Measured with and without, complex128 N = 20: 170 and 188 us per fourth-order step; complex64
-// N = 19: 28.8 and 30.2 us per second-order step.
+// workgroups leaves each CU one of them; its time is the latency of the chain of stages, which a
+// full buffer, or two (one barrier per transpose), and more registers shorten.  It stays within
+// half a CU all the same (registers too: the bound on waves per SIMD), so that launches on other
+// streams run beside it: at kConeFewTiles and four streams (the hardware queues of a process)
+// every workgroup still finds a place at once.
+// Eight fourth-order steps of a complex128 chain, us, this form against the other: N = 18 1140
+// and 1266, N = 19 1205 and 1336 (four streams at once 2730 and 3100); N = 20, 256 workgroups,
+// 1353 and 1500 alone but 3100 and 2300 on four streams.  Two full buffers in complex128 (139 KB,
+// one workgroup per CU) took 1209 at N = 19 and 3220 on four streams.
 template <typename R, bool FEW>
 using ConeLds = typename std::conditional<sizeof(R) == 8, typename std::conditional<FEW, double2, double>::type, float2>::type;
+template <typename R, int T, bool FEW>
+__host__ __device__ constexpr int cone_lds()
+{
+    return FEW && cone_two_buffers<T, ConeLds<R, FEW>>() ? 2 * cone_buffer(T) : cone_buffer(T);
+}
 template <typename R, int T, int RB, bool FEW>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(FEW ? 1 : 4)))
+__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(FEW ? T - 10 : 4)))
 void cone_kernel(typename Vec<R>::T *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
                  int reverse)
 {
-    constexpr int HB = (1 << T) + (1 << T) / 16;
-    __shared__ ConeLds<R, FEW> lds[FEW ? 2 * HB : HB];
+    __shared__ ConeLds<R, FEW> lds[cone_lds<R, T, FEW>()];
     const uint64_t tile = reverse ? n_tiles - 1 - blockIdx.x : blockIdx.x;
     cone_sweep<R, T, RB, ConeLds<R, FEW>, false, FEW>(psi, a, tile, lds);
 }
@@ -1493,12 +1511,11 @@ void cone_kernel(typename Vec<R>::T *__restrict__ psi, const ConeArgs *__restric
 // The last sweep of a vector's recorded segment, with the segment's observables (complex128:
 // three waves per SIMD, four would spill).
 template <typename R, int T, int RB, bool FEW>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(FEW ? 1 : sizeof(R) == 8 ? 3 : 4)))
+__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(FEW ? T - 10 : sizeof(R) == 8 ? 3 : 4)))
 void cone_rec_kernel(typename Vec<R>::T *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
                      int reverse, ConeRec rec)
 {
-    constexpr int HB = (1 << T) + (1 << T) / 16;
-    __shared__ ConeLds<R, FEW> lds[FEW ? 2 * HB : HB];
+    __shared__ ConeLds<R, FEW> lds[cone_lds<R, T, FEW>()];
     __shared__ double red[2 << (T - RB - 6)];
     const uint64_t tile = reverse ? n_tiles - 1 - blockIdx.x : blockIdx.x;
     cone_sweep<R, T, RB, ConeLds<R, FEW>, true, FEW>(psi, a, tile, lds, &rec, red);
