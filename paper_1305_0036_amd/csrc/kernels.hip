@@ -1139,37 +1139,93 @@ __device__ __forceinline__ void cone_diag(V (&x)[1 << RB], ctab wgf, double2 w0,
             if (!FEW && (j & 3) == 3) __builtin_amdgcn_sched_barrier(0);
         }
     } else {
-        // complex64: one product and one rounding per amplitude whatever the mask, by the same
-        // operations for a given mask always (see resident_diag_kernel): the registers in
-        // Gray-code order, four at a time (FEW: all at once), and other masks walk along, P[0]
-        // the walk's factor (its steps formed where they are used: held, they would not fit the
-        // registers)
-        constexpr int G = FEW ? 1 << RB : 4;
+        // complex64 of few tiles: one product and one rounding per amplitude whatever the mask, by
+        // the operations of cone_diag_cm and cone_diag_walk for that mask: the registers in
+        // Gray-code order, and other masks walk along, P[0] the walk's factor
+        double2 z[1 << RB];
+        if (inner) {
 #pragma unroll
-        for (int k0 = 0; k0 < (1 << RB); k0 += G) {
-            double2 z[G];
-            if (inner) {
-#pragma unroll
-                for (int e = 0; e < G; ++e) {
-                    const int k = k0 + e, j = k ^ (k >> 1), v = k ? __builtin_ctz(k) : 0;
-                    if (k > 0) {
-                        const double2 f = bit_factor(v);
-                        P[0] = cmul(P[0], ((j >> v) & 1) ? f : make_double2(f.x, -f.y));
-                    }
-                    z[e] = cmul(P[0], ld2(q, j));
+            for (int k = 0; k < (1 << RB); ++k) {
+                const int j = k ^ (k >> 1), v = k ? __builtin_ctz(k) : 0;
+                if (k > 0) {
+                    const double2 f = bit_factor(v);
+                    P[0] = cmul(P[0], ((j >> v) & 1) ? f : make_double2(f.x, -f.y));
                 }
-            } else {
-#pragma unroll
-                for (int e = 0; e < G; ++e) {
-                    const int k = k0 + e, j = k ^ (k >> 1);
-                    z[e] = cmul(P[(j & 1) | ((j >> (RB - 1)) << 1)], ld2(q, j));
-                }
+                z[k] = cmul(P[0], ld2(q, j));
             }
+        } else {
 #pragma unroll
-            for (int e = 0; e < G; ++e) apply_cone(x[(k0 + e) ^ ((k0 + e) >> 1)], z[e]);
-            if (!FEW) __builtin_amdgcn_sched_barrier(0);
+            for (int k = 0; k < (1 << RB); ++k) {
+                const int j = k ^ (k >> 1);
+                z[k] = cmul(P[(j & 1) | ((j >> (RB - 1)) << 1)], ld2(q, j));
+            }
         }
+#pragma unroll
+        for (int k = 0; k < (1 << RB); ++k) apply_cone(x[k ^ (k >> 1)], z[k]);
     }
+}
+
+// The phase step of complex64 sweeps of many tiles: a copy of the products per mask.  The
+// amplitudes take half the registers of complex128, so four waves per SIMD fit anyway (110
+// registers), and the one path above, four products at a time to keep its registers, is slower:
+// N = 27 chain 10.56 against 10.82 ms per fourth-order step, N = 26 with next-nearest bonds 6.31
+// and 7.44.  First any mask, as a Gray-code walk over the registers (flipping bit v up multiplies
+// by the square of its two factors; exactly 1 + 0i for a bit without couplings).
+template <int T, int RB, typename V>
+__device__ __forceinline__ void cone_diag_walk(V (&x)[1 << RB], ctab wgf, double2 w0, ctab q,
+                                               const double2 (&th)[1 + RB], uint32_t xmask, int w)
+{
+    const uint32_t tid = threadIdx.x;
+    const uint32_t t0 = thread_part<RB>(tid, w);
+    double2 p = cmul(w0, th[0]);
+    uint32_t m = xmask & ~(((1u << RB) - 1u) << w);
+    while (m) {
+        const int k = __builtin_ctz(m);
+        m &= m - 1u;
+        const double2 G = ld2(wgf, 1 + k);
+        p = cmul(p, ((t0 >> k) & 1) ? G : make_double2(G.x, -G.y));
+    }
+    double2 wv[RB];
+#pragma unroll
+    for (int v = 0; v < RB; ++v) wv[v] = cmul(ld2(wgf, 1 + w + v), th[1 + v]);
+#pragma unroll
+    for (int k = 0; k < (1 << RB); ++k) {
+        const int j = k ^ (k >> 1);
+        if (k > 0) {
+            const int v = __builtin_ctz(k);
+            p = cmul(p, ((j >> v) & 1) ? wv[v] : make_double2(wv[v].x, -wv[v].y));
+        }
+        apply_cone(x[j], cmul(p, ld2(q, j)));
+    }
+}
+// ... and the masks in which only the window bits in CM (known when compiling) have walk
+// factors other than exactly 1 + 0i: the products P[s] = p * prod_{v in s} wv[v] over the
+// subsets s of CM (2^|CM| - 1 complex products), and register j takes P[j & CM] * q[j].
+template <int T, int RB, uint32_t CM, typename V>
+__device__ __forceinline__ void cone_diag_cm(V (&x)[1 << RB], ctab wgf, double2 w0, ctab q,
+                                             const double2 (&th)[1 + RB], uint32_t xmask, int w)
+{
+    const uint32_t t0 = thread_part<RB>(threadIdx.x, w);
+    double2 P[1 << RB];
+    P[0] = cmul(w0, th[0]);
+    uint32_t m = xmask & ~(((1u << RB) - 1u) << w);
+    while (m) {
+        const int k = __builtin_ctz(m);
+        m &= m - 1u;
+        const double2 G = ld2(wgf, 1 + k);
+        P[0] = cmul(P[0], ((t0 >> k) & 1) ? G : make_double2(G.x, -G.y));
+    }
+#pragma unroll
+    for (int v = 0; v < RB; ++v) {
+        if (!((CM >> v) & 1u)) continue;
+        const double2 f = cmul(ld2(wgf, 1 + w + v), th[1 + v]);
+        const uint32_t lower = CM & ((1u << v) - 1u);
+#pragma unroll
+        for (uint32_t s = 0; s < (1u << RB); ++s)
+            if ((s & ~lower) == 0) P[s | (1u << v)] = cmul(P[s], f);
+    }
+#pragma unroll
+    for (int j = 0; j < (1 << RB); ++j) apply_cone(x[j], cmul(P[j & CM], ld2(q, j)));
 }
 
 // ... on two vectors (the adjoint's psi and lambda), each factor formed once; the row and the
@@ -1360,7 +1416,7 @@ __device__ __forceinline__ void cone_thread_row(const ConeArgs *__restrict__ a, 
         if ((need >> v) & 1u) th[1 + v] = gload2(dt, (size_t)row * (1 + RB) + 1 + v);
 }
 
-// The same for the one-vector sweep: the row's address, entry 0, and the entries of the lowest
+// The same for cone_diag: the row's address, entry 0, and the entries of the lowest
 // and the highest window bit where the step's walk mask is one of those two (or both); any
 // other mask loads its entries when it gets there (cone_diag).
 template <int RB>
@@ -1443,9 +1499,15 @@ __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
         const int p = (int)((code >> 9) & 63u);
         // the thread's phase-table row is loaded first: its latency then hides behind the
         // transpose and the butterflies of the stage
-        double2 th[3];
+        constexpr bool MASKS = sizeof(R) == 4 && !FEW;
+        double2 th[MASKS ? 1 + RB : 3];
         gtab row = nullptr;
-        if (has_phase) row = cone_thread_ends<RB>(a, code, th);
+        if (has_phase) {
+            if constexpr (MASKS)
+                cone_thread_row<RB>(a, code, th);
+            else
+                row = cone_thread_ends<RB>(a, code, th);
+        }
         if (w != cur) {
             transpose(w);
             cur = w;
@@ -1459,7 +1521,17 @@ __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
             const ctab wp = as_const(ph.wgf) + 2 * cone_row(ph, tile) * (T + 1);
             const double2 w0 = cmul(make_double2(ph.kre, ph.kim), ld2(wp, 0));
             const ctab qp = as_const(ph.dtab) + 2 * (1u << (T - RB)) * (1 + RB);
-            cone_diag<T, RB, FEW>(x, wp, w0, qp, th, ph.cmask, ph.xmask, row, w);
+            if constexpr (MASKS) {
+                switch (ph.cmask) {
+                case 0: cone_diag_cm<T, RB, 0u>(x, wp, w0, qp, th, ph.xmask, w); break;
+                case 1: cone_diag_cm<T, RB, 1u>(x, wp, w0, qp, th, ph.xmask, w); break;
+                case 8: cone_diag_cm<T, RB, 8u>(x, wp, w0, qp, th, ph.xmask, w); break;
+                case 9: cone_diag_cm<T, RB, 9u>(x, wp, w0, qp, th, ph.xmask, w); break;
+                default: cone_diag_walk<T, RB>(x, wp, w0, qp, th, ph.xmask, w); break;
+                }
+            } else {
+                cone_diag<T, RB, FEW>(x, wp, w0, qp, th, ph.cmask, ph.xmask, row, w);
+            }
         }
     }
     if (cur != a->store_win) transpose(a->store_win);
@@ -1508,10 +1580,10 @@ void cone_kernel(typename Vec<R>::T *__restrict__ psi, const ConeArgs *__restric
     cone_sweep<R, T, RB, ConeLds<R, FEW>, false, FEW>(psi, a, tile, lds);
 }
 
-// The last sweep of a vector's recorded segment, with the segment's observables (complex128:
-// three waves per SIMD, four would spill).
+// The last sweep of a vector's recorded segment, with the segment's observables (at four waves per
+// SIMD its registers would spill; complex64 N = 21 511 against 527 us per two recorded steps).
 template <typename R, int T, int RB, bool FEW>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(FEW ? T - 10 : sizeof(R) == 8 ? 3 : 4)))
+__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(FEW ? T - 10 : 3)))
 void cone_rec_kernel(typename Vec<R>::T *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
                      int reverse, ConeRec rec)
 {
