@@ -318,9 +318,9 @@ uint64_t deposit(uint64_t x, uint64_t mask)
 
 // ------------------------------------------------------------------ light-cone plan
 
-static bool cone_plan(const FoldedChain &fc, int n, int T, int s,
-                      const std::vector<std::pair<int, int>> &bonds, int max_adv, size_t max_sweeps,
-                      ConePlan &out, int max_phases, bool even)
+bool make_cone_plan(const FoldedChain &fc, int n, int T, int s,
+                    const std::vector<std::pair<int, int>> &bonds, int max_adv, size_t max_sweeps,
+                    ConePlan &out, int max_phases, bool even)
 {
     if (n <= T || n > 62 || s < 1 || s >= T) return false;
     const int m = fc.n_layers;
@@ -349,7 +349,8 @@ static bool cone_plan(const FoldedChain &fc, int n, int T, int s,
     const int nw = (int)starts.size();
     // windows spread evenly instead of the last one short: consecutive windows then share more
     // spins, and a sweep carries its light cone further (xyz chain, N = 23 and 24: 8 sweeps
-    // instead of 9 for one step, 25 instead of 33 for four; N = 19, 20, 27, 28: the same windows)
+    // instead of 9 for one step, 25 instead of 33 for four; N = 19, 20, 27, 28: the same
+    // windows).  They may share too few spins to hand the low memory bits on.
     if (even)
         for (int w = 1; w + 1 < nw; ++w) starts[w] = (2 * w * (n - T) + nw - 1) / (2 * (nw - 1));
     std::vector<int> order;
@@ -585,16 +586,6 @@ static bool cone_plan(const FoldedChain &fc, int n, int T, int s,
     for (int q = 0; q < n; ++q)
         if (pos[q] != q) return false;
     return true;
-}
-
-// Evenly spread windows may share too few spins to hand the low memory bits on; the packed ones
-// then stand in.
-bool make_cone_plan(const FoldedChain &fc, int n, int T, int s,
-                    const std::vector<std::pair<int, int>> &bonds, int max_adv, size_t max_sweeps,
-                    ConePlan &out, int max_phases, bool even)
-{
-    return (even && cone_plan(fc, n, T, s, bonds, max_adv, max_sweeps, out, max_phases, true)) ||
-           cone_plan(fc, n, T, s, bonds, max_adv, max_sweeps, out, max_phases, false);
 }
 
 }  // namespace ts

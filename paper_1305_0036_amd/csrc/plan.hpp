@@ -173,7 +173,7 @@ struct ConePlan {
 // Light-cone plan of a folded chain for n spins, tiles of T bits of which the s lowest
 // memory bits are in every tile, bonds (i, j) as listed (duplicates allowed).  max_adv
 // bounds the layers one spin takes in one sweep and max_phases the phase steps of one sweep
-// (<= 0: no bound); even spreads the windows evenly.  Returns false (and
+// (<= 0: no bound); even spreads the windows evenly (else they are packed).  Returns false (and
 // leaves `out` unspecified) when the windows cannot cover the spins under these rules:
 // n <= T, s >= T, or a plan longer than max_sweeps.
 bool make_cone_plan(const FoldedChain &fc, int n, int T, int s,

@@ -86,6 +86,7 @@ struct PlanEntry {
     // light-cone form of the same run (used instead of `plan` when `cone` is set)
     bool cone = false;
     double cone_cost = 0.0;                // the cost model's time of the light-cone form (us)
+    int cone_even = 0;                     // its windows: packed from the left, or spread evenly
     ts::ConePlan cone_plan;
     DevBuf cone_dev;                       // tsk::ConeArgs[] of every sweep
     std::vector<tsk::ConeArgs> cone_host;  // host copy (batched launches gather them)
@@ -329,29 +330,22 @@ double pingpong_sweep_us(int dtype, int T)
     if (dtype == TS_C128) return T >= 13 ? 1000.0 : 790.0;
     return T >= 14 ? 550.0 : T == 13 ? 480.0 : 415.0;
 }
+constexpr double kLaunchUs = 8.0;
 bool cone_stages(const ts::ConeSweep &sw, int T, int RB, int s, tsk::ConeArgs &a,
                  std::vector<int> &phase_win, int *transposes);
 
-// Light-cone windows spread evenly (fewer sweeps).  complex64 keeps the windows packed from the
-// left: its roundings depend on which sweep takes which layer, and its results stay what they were.
-bool even_windows(int dtype) { return dtype == TS_C128; }
-
-bool cone_candidate(ts_ctx *c, PlanEntry *pe, int T, int dtype, int mode)
+// The model's time (us) of a light-cone plan's sweeps, or a negative number where the kernel cannot
+// run them.
+double cone_cost(const ts_ctx *c, const ts::ConePlan &cp, int dtype)
 {
-    std::vector<std::pair<int, int>> bonds;
-    for (size_t k = 0; k < c->bi.size(); ++k) bonds.push_back({c->bi[k], c->bj[k]});
-    ts::ConePlan cp;
-    const size_t limit = 4 * pe->plan.sweeps.size() + 16;
-    if (!ts::make_cone_plan(pe->plan.chain, c->n, T, kConeLowBits, bonds, c->cone_adv, limit, cp,
-                            tsk::kConePhases, even_windows(dtype)))
-        return false;
+    const int T = cp.T;
     double cost = 0.0;
     for (const ts::ConeSweep &sw : cp.sweeps) {
         tsk::ConeArgs a;
         std::vector<int> pw;
         int tr = 0;
-        if (sw.phases.size() > (size_t)tsk::kConePhases || !cone_stages(sw, T, 4, kConeLowBits, a, pw, &tr))
-            return false;  // does not fit the kernel's limits: keep the ping-pong plan
+        if (sw.phases.size() > (size_t)tsk::kConePhases || !cone_stages(sw, T, 4, cp.s, a, pw, &tr))
+            return -1.0;  // does not fit the kernel's limits
         // a phase step selects its workgroup row by the bits of the outside spins its
         // bonds reach; the kernel holds kConeRowBits of them
         std::vector<char> in_tile(c->n, 0);
@@ -362,7 +356,7 @@ bool cone_candidate(ts_ctx *c, PlanEntry *pe, int T, int dtype, int mode)
                 const int p = c->bi[b], q = c->bj[b];
                 if (in_tile[p] != in_tile[q]) outside |= 1ull << (in_tile[p] ? q : p);
             }
-            if (__builtin_popcountll(outside) > tsk::kConeRowBits) return false;
+            if (__builtin_popcountll(outside) > tsk::kConeRowBits) return -1.0;
         }
         int sl = 0;
         for (const ts::ConeOp &op : sw.ops)
@@ -371,13 +365,53 @@ bool cone_candidate(ts_ctx *c, PlanEntry *pe, int T, int dtype, int mode)
         cost += dtype == TS_C128 ? 526.0 + 30.3 * tr + 40.1 * ph + 11.3 * sl
                                  : 201.0 + 8.3 * tr + 41.5 * ph + 11.9 * sl;
     }
+    return cost * std::ldexp(1.0, c->n - 27) + kLaunchUs * (double)cp.sweeps.size();
+}
+
+// Light-cone plan of a chain, with the windows packed from the left or (complex128) spread evenly.
+// Evenly spread windows often need fewer sweeps (the xyz chain at N = 23, four steps: 25 instead of
+// 33), but not always (five first-order steps of a chain of 29 spins: 12 instead of 10), so they
+// are taken where the model finds them cheaper.  Measured over chains, next-nearest bonds and
+// ladders of 14 to 29 spins it never ranks the two wrongly by more than 1%; even against packed
+// N = 23 next-nearest bonds 0.82 (model 0.86), N = 26 a three-wide ladder 1.07 (1.08), N = 29 a
+// chain, first order, 1.19 (1.08).  complex64 keeps the packed windows: its roundings depend on
+// which sweep takes which layer, and its results stay what they were.  even: -1 as the model says,
+// else 0 or 1; the choice comes back in it.  *cost < 0: a plan, but none that the kernel can run.
+bool cone_windows(const ts_ctx *c, const ts::FoldedChain &chain, int T, int s, int dtype, int max_adv,
+                  size_t limit, int *even, ts::ConePlan &out, double *cost)
+{
+    std::vector<std::pair<int, int>> bonds;
+    for (size_t k = 0; k < c->bi.size(); ++k) bonds.push_back({c->bi[k], c->bj[k]});
+    const int want = dtype == TS_C128 ? *even : 0;
+    *even = -1;
+    for (int w = 0; w < 2; ++w) {
+        if (want >= 0 && w != want) continue;
+        ts::ConePlan cp;
+        if (!ts::make_cone_plan(chain, c->n, T, s, bonds, max_adv, limit, cp, tsk::kConePhases, w == 1)) continue;
+        const double t = cone_cost(c, cp, dtype);
+        if (*even >= 0 && (t < 0.0 || (*cost >= 0.0 && t >= 0.985 * *cost))) continue;
+        *even = w;
+        *cost = t;
+        out = std::move(cp);
+    }
+    return *even >= 0;
+}
+
+// like: another plan whose choice of windows this one follows (chains of one batch class).
+bool cone_candidate(ts_ctx *c, PlanEntry *pe, int T, int dtype, int mode, const PlanEntry *like = nullptr)
+{
+    ts::ConePlan cp;
+    double cost;
+    int even = like ? like->cone_even : -1;
+    const size_t limit = 4 * pe->plan.sweeps.size() + 16;
+    if (!cone_windows(c, pe->plan.chain, T, kConeLowBits, dtype, c->cone_adv, limit, &even, cp, &cost) || cost < 0.0)
+        return false;  // keep the ping-pong plan
     const double pp = (double)pe->plan.sweeps.size() * pingpong_sweep_us(dtype, T);
-    const double scale = std::ldexp(1.0, c->n - 27), launch = 8.0;
-    cost = cost * scale + launch * (double)cp.sweeps.size();
-    const double ppc = pp * scale + launch * (double)pe->plan.sweeps.size();
+    const double ppc = pp * std::ldexp(1.0, c->n - 27) + kLaunchUs * (double)pe->plan.sweeps.size();
     if (mode == 1 && cost >= 0.95 * ppc) return false;
     pe->cone_plan = std::move(cp);
     pe->cone_cost = cost;
+    pe->cone_even = even;
     return true;
 }
 
@@ -2204,7 +2238,7 @@ ts_status build_batch_program(ts_ctx *ctx, char *psi_packed, const int64_t *psi_
                 PlanEntry *pe;
                 ts_ctx *cm = ctx->chains[m].get();
                 if (build_plan(cm, dtype, Tdef, order, dt, steps, &pe) != TS_OK) return false;
-                if (!pe->cone) pe->cone = cone_candidate(cm, pe, Tdef, dtype, 2);
+                if (!pe->cone) pe->cone = cone_candidate(cm, pe, Tdef, dtype, 2, &probe);
                 if (!pe->cone || pe->cone_plan.sweeps.size() != probe.cone_plan.sweeps.size()) return false;
                 if (prepare_cone(cm, pe, dtype) != TS_OK) return false;
                 pes.push_back(pe);
@@ -2765,10 +2799,9 @@ ts_status ts_cone_describe(ts_ctx *ctx, ts_dtype dtype, double dt, int64_t nstep
     } catch (const std::exception &e) {
         return fail(TS_EINVAL, std::string("plan: ") + e.what());
     }
-    std::vector<std::pair<int, int>> bonds;
-    for (size_t k = 0; k < ctx->bi.size(); ++k) bonds.push_back({ctx->bi[k], ctx->bj[k]});
-    if (!ts::make_cone_plan(P.chain, ctx->n, T, s, bonds, max_adv, 1u << 20, cp, tsk::kConePhases,
-                           even_windows(dtype)))
+    double cost;
+    int even = -1;
+    if (!cone_windows(ctx, P.chain, T, s, dtype, max_adv, 1u << 20, &even, cp, &cost))
         return fail(TS_EINVAL, "no light-cone plan for these sizes");
     if (used) {
         *used = 0;
@@ -2832,7 +2865,7 @@ ts_status ts_cone_describe(ts_ctx *ctx, ts_dtype dtype, double dt, int64_t nstep
             const ts::ConePhase &ph = sw.phases[op.phase];
             const ts::DiagStep &d = cp.chain.diags[ph.level];
             int64_t bm = 0;
-            if (bonds.size() <= 63) {
+            if (ctx->bi.size() <= 63) {
                 for (int b : ph.bonds) bm |= 1ll << b;
             } else {
                 bm = -1;
