@@ -104,11 +104,29 @@ struct PlanEntry {
 // Phase factors of one light-cone phase step (restricted terms): workgroup rows and the
 // per-thread / window table.
 struct ConeTab {
-    DevBuf wgf, dtab;
+    size_t wgf_at = 0, dtab_at = 0;                  // where they are in the buffer of the upload
+    const double *wgf = nullptr, *dtab = nullptr;    // device, once that is uploaded
     int8_t row_bit[tsk::kConeRowBits] = {};
     int n_row_bits = 0;
     uint32_t xmask = 0;   // tile bits with a row-dependent field
     uint32_t cmask = 0;   // window bits with a thread- or workgroup-dependent walk factor
+};
+
+// Tables on their way to the device: formed in a host buffer, and uploaded a megabyte at a time.  A
+// plan can need some hundred (125 to 275 for eight steps of a chain of 23 spins), and two
+// allocations and two blocking copies for each took as long as forming them.
+struct ConeUpload {
+    static constexpr size_t kBytes = (size_t)1 << 20;
+    std::vector<ts::cplx> host;
+    std::map<std::string, std::unique_ptr<ConeTab>> tabs;
+    // room for a table, at a multiple of 256 bytes
+    size_t add(size_t entries)
+    {
+        if (host.empty()) host.reserve((2 * kBytes) / sizeof(ts::cplx));
+        const size_t at = (host.size() + 15) / 16 * 16;
+        host.resize(at + entries);
+        return at;
+    }
 };
 
 }  // namespace
@@ -135,6 +153,7 @@ struct ts_ctx {
     double watchdog = -1.0;                     // ts_evolve norm-drift bound (< 0: off)
     DevBuf watch_buf;                           // norms before and after, [2][n_psi]
     std::map<std::string, std::unique_ptr<ConeTab>> cone_tabs;
+    std::vector<std::unique_ptr<DevBuf>> cone_bufs;   // what they point to
     bool tune_checked[2] = {false, false};      // tuning cache consulted for this dtype
     bool user_config[2] = {false, false};       // tile width set explicitly: keep it
     std::map<std::tuple<int, uint64_t, int>, std::unique_ptr<EnergyTable>> tables;
@@ -851,7 +870,7 @@ ts_status prepare_sweeps(ts_ctx *c, PlanEntry *pe, int dtype)
 // outside spin's bit: those bits (their workgroup-index positions in `rank`) select the row.
 ts_status get_cone_tab(ts_ctx *c, int T, int RB, int w, const std::vector<int> &tile_q,
                        const std::vector<int> &rank, int axis, double tau, int qturn, uint64_t own,
-                       const std::vector<int> &bonds, const ConeTab **out)
+                       const std::vector<int> &bonds, ConeUpload &up, const ConeTab **out)
 {
     const int n = c->n;
     std::vector<int> kof(n, -1);
@@ -891,18 +910,17 @@ ts_status get_cone_tab(ts_ctx *c, int T, int RB, int w, const std::vector<int> &
     uint32_t qmask = 0;
     for (int q = 0; q < n; ++q)
         if ((own >> q) & 1) qmask |= 1u << kof[q];
-    uint64_t tb;
-    std::memcpy(&tb, &tau, sizeof tb);
-    std::string key = std::to_string(T) + "/" + std::to_string(RB) + "/" + std::to_string(w) + "/" +
-                      std::to_string(axis) + "/" + std::to_string(tb) + "/" + std::to_string(qturn & 3) + "/" +
-                      std::to_string(qmask) + "|";
-    for (int q : tile_q) key += std::to_string(q) + ",";
-    key += "|";
-    for (int b : bonds) key += std::to_string(b) + ",";
-    key += "|";
-    for (int p : partners) key += std::to_string(rank[p]) + ",";
-    auto it = c->cone_tabs.find(key);
-    if (it != c->cone_tabs.end()) {
+    std::string key;
+    auto put = [&](const void *x, size_t bytes) { key.append(static_cast<const char *>(x), bytes); };
+    const int32_t head[] = {T, RB, w, axis, qturn & 3, (int32_t)qmask, (int32_t)bonds.size(), (int32_t)partners.size()};
+    put(head, sizeof head);
+    put(&tau, sizeof tau);
+    put(tile_q.data(), tile_q.size() * sizeof(int));
+    put(bonds.data(), bonds.size() * sizeof(int));
+    for (int p : partners) put(&rank[p], sizeof(int));
+    for (const auto *tabs : {&c->cone_tabs, &up.tabs}) {
+        auto it = tabs->find(key);
+        if (it == tabs->end()) continue;
         *out = it->second.get();
         return TS_OK;
     }
@@ -916,7 +934,11 @@ ts_status get_cone_tab(ts_ctx *c, int T, int RB, int w, const std::vector<int> &
     auto in_win = [&](int k) { return k >= w && k < w + RB; };
     // workgroup rows: the fields that bonds to outside spins put on tile bits
     const int nr = (int)partners.size();
-    std::vector<ts::cplx> rows((size_t)(1u << nr) * (T + 1));
+    auto ct = std::make_unique<ConeTab>();
+    const int nthr = 1 << (T - RB);
+    ct->wgf_at = up.add((size_t)(1u << nr) * (T + 1));
+    ct->dtab_at = up.add((size_t)nthr * (1 + RB) + (1u << RB));
+    ts::cplx *const rows = &up.host[ct->wgf_at], *const tab = &up.host[ct->dtab_at];
     uint32_t xmask = 0;
     for (const Cross &x : cross) xmask |= 1u << x.k;
     for (uint32_t r = 0; r < (1u << nr); ++r) {
@@ -931,27 +953,51 @@ ts_status get_cone_tab(ts_ctx *c, int T, int RB, int w, const std::vector<int> &
         }
         row[0] = ex(-0.5 * gw);
     }
-    // per-thread and window tables
-    const int nthr = 1 << (T - RB);
-    std::vector<ts::cplx> tab((size_t)nthr * (1 + RB) + (1u << RB));
+    // per-thread and window tables.  A step holds few terms: only those are summed, and a thread
+    // takes its factor from the thread pattern with the same bits where its terms read them and
+    // zeros elsewhere.
+    struct Term { int k1, k2; double x; };   // k2 < 0: a field
+    std::vector<Term> terms, win_terms[4];   // outside the window; its bit v with outside bits
+    uint32_t rel = 0, win_rel[4] = {};       // the bits that they read (rel: all of them)
+    for (int k1 = 0; k1 < T; ++k1) {
+        if (in_win(k1)) continue;
+        if (hf[k1] != 0.0) terms.push_back({k1, -1, hf[k1]});
+        for (int k2 = k1 + 1; k2 < T; ++k2)
+            if (!in_win(k2) && J(k1, k2) != 0.0) terms.push_back({k1, k2, J(k1, k2)});
+        for (int v = 0; v < RB; ++v)
+            if (J(k1, w + v) != 0.0) {
+                win_terms[v].push_back({k1, -1, J(k1, w + v)});
+                win_rel[v] |= 1u << k1;
+            }
+    }
+    for (const Term &t : terms) rel |= (1u << t.k1) | (t.k2 < 0 ? 0u : 1u << t.k2);
+    for (int v = 0; v < RB; ++v) rel |= win_rel[v];
+    auto thread_of = [&](uint32_t t) { return (t & ((1u << w) - 1u)) | ((t >> (w + RB)) << w); };
+    std::vector<ts::cplx> own_e(nthr);
+    std::vector<std::array<double, 4>> h(nthr);
     for (int tid = 0; tid < nthr; ++tid) {
         const uint32_t t0 = (tid & ((1u << w) - 1u)) | ((uint32_t)(tid >> w) << (w + RB));
-        double e = 0.0;
-        for (int k1 = 0; k1 < T; ++k1) {
-            if (in_win(k1)) continue;
-            e += hf[k1] * sp(t0, k1);
-            for (int k2 = k1 + 1; k2 < T; ++k2)
-                if (!in_win(k2)) e += J(k1, k2) * sp(t0, k1) * sp(t0, k2);
-        }
-        double hw = 0.0;
+        ts::cplx *row = &tab[(size_t)tid * (1 + RB)];
         for (int v = 0; v < RB; ++v) {
-            double h = 0.0;
-            for (int k = 0; k < T; ++k)
-                if (!in_win(k)) h += J(k, w + v) * sp(t0, k);
-            tab[(size_t)tid * (1 + RB) + 1 + v] = ex(h);
-            hw += h;
+            if (const uint32_t same = thread_of(t0 & win_rel[v]); same != (uint32_t)tid) {
+                h[tid][v] = h[same][v];
+                row[1 + v] = tab[(size_t)same * (1 + RB) + 1 + v];
+                continue;
+            }
+            double x = 0.0;
+            for (const Term &t : win_terms[v]) x += t.x * sp(t0, t.k1);
+            h[tid][v] = x;
+            row[1 + v] = ex(x);
         }
-        tab[(size_t)tid * (1 + RB)] = qt(qturn * __builtin_popcount(t0 & qmask)) * ex(e - 0.5 * hw);
+        if (const uint32_t same = thread_of(t0 & rel); same != (uint32_t)tid) {
+            own_e[tid] = own_e[same];
+        } else {
+            double e = 0.0, hw = 0.0;
+            for (const Term &t : terms) e += t.k2 < 0 ? t.x * sp(t0, t.k1) : t.x * sp(t0, t.k1) * sp(t0, t.k2);
+            for (int v = 0; v < RB; ++v) hw += h[tid][v];
+            own_e[tid] = ex(e - 0.5 * hw);
+        }
+        row[0] = qt(qturn * __builtin_popcount(t0 & qmask)) * own_e[tid];
     }
     for (uint32_t r = 0; r < (1u << RB); ++r) {
         double e = 0.0;
@@ -961,23 +1007,35 @@ ts_status get_cone_tab(ts_ctx *c, int T, int RB, int w, const std::vector<int> &
         }
         tab[(size_t)nthr * (1 + RB) + r] = qt(qturn * __builtin_popcount((r << w) & qmask)) * ex(e);
     }
-    auto ct = std::make_unique<ConeTab>();
     ct->xmask = xmask;
     for (int v = 0; v < RB; ++v) {
         bool dep = (xmask >> (w + v)) & 1;
         for (int k = 0; k < T && !dep; ++k) dep = !in_win(k) && J(k, w + v) != 0.0;
         if (dep) ct->cmask |= 1u << v;
     }
-    ts_status st = alloc(ct->wgf, rows.size() * sizeof(ts::cplx));
-    if (st != TS_OK) return st;
-    st = alloc(ct->dtab, tab.size() * sizeof(ts::cplx));
-    if (st != TS_OK) return st;
-    TS_HIP(hipMemcpy(ct->wgf.p, rows.data(), rows.size() * sizeof(ts::cplx), hipMemcpyHostToDevice));
-    TS_HIP(hipMemcpy(ct->dtab.p, tab.data(), tab.size() * sizeof(ts::cplx), hipMemcpyHostToDevice));
     ct->n_row_bits = nr;
     for (int i = 0; i < nr; ++i) ct->row_bit[i] = (int8_t)rank[partners[i]];
     *out = ct.get();
-    c->cone_tabs.emplace(key, std::move(ct));
+    up.tabs.emplace(key, std::move(ct));
+    return TS_OK;
+}
+
+// Uploads the tables formed so far into a buffer of the context.
+ts_status upload_cone_tabs(ts_ctx *c, ConeUpload &up)
+{
+    if (up.host.empty()) return TS_OK;
+    auto buf = std::make_unique<DevBuf>();
+    ts_status st = alloc(*buf, up.host.size() * sizeof(ts::cplx));
+    if (st != TS_OK) return st;
+    TS_HIP(hipMemcpy(buf->p, up.host.data(), up.host.size() * sizeof(ts::cplx), hipMemcpyHostToDevice));
+    const double *at = static_cast<const double *>(buf->p);
+    c->cone_bufs.push_back(std::move(buf));
+    for (auto &t : up.tabs) {
+        t.second->wgf = at + 2 * t.second->wgf_at;
+        t.second->dtab = at + 2 * t.second->dtab_at;
+    }
+    c->cone_tabs.merge(up.tabs);
+    up.host.clear();
     return TS_OK;
 }
 
@@ -1143,6 +1201,8 @@ ts_status prepare_cone(ts_ctx *c, PlanEntry *pe, int dtype)
     const int n = c->n, T = P.T, RB = c->reg_bits[dtype];
     if (RB != 4) return fail(TS_EINVAL, "internal: light-cone sweeps need 16 amplitudes per thread");
     std::vector<tsk::ConeArgs> args(P.sweeps.size());
+    ConeUpload up;
+    std::vector<std::pair<tsk::ConePhaseArgs *, const ConeTab *>> steps;
     pe->cone_phase_win.assign(P.sweeps.size(), {});
     std::vector<int> pos(n);
     for (int q = 0; q < n; ++q) pos[q] = q;
@@ -1186,9 +1246,11 @@ ts_status prepare_cone(ts_ctx *c, PlanEntry *pe, int dtype)
             const ts::DiagStep &d = P.chain.diags[ph.level];
             const ConeTab *tab;
             ts_status st = get_cone_tab(c, T, RB, pw[p], sw.tile_q, rank, d.axis, d.tau, d.qturn, ph.own,
-                                        ph.bonds, &tab);
+                                        ph.bonds, up, &tab);
+            if (st == TS_OK && up.host.size() * sizeof(ts::cplx) >= ConeUpload::kBytes) st = upload_cone_tabs(c, up);
             if (st != TS_OK) return st;
             tsk::ConePhaseArgs &pa = a.ph[p];
+            steps.push_back({&pa, tab});
             static const double r2 = 0.70710678118654752440;
             static const double cs[8] = {1, r2, 0, -r2, -1, -r2, 0, r2};
             static const double sn[8] = {0, r2, 1, r2, 0, -r2, -1, -r2};
@@ -1196,8 +1258,6 @@ ts_status prepare_cone(ts_ctx *c, PlanEntry *pe, int dtype)
             if (ph.half_scale & 1) mag *= r2;
             pa.kre = mag * cs[ph.eighths & 7];
             pa.kim = mag * sn[ph.eighths & 7];
-            pa.wgf = static_cast<const double *>(tab->wgf.p);
-            pa.dtab = static_cast<const double *>(tab->dtab.p);
             pa.n_row_bits = tab->n_row_bits;
             pa.xmask = tab->xmask;
             pa.cmask = tab->cmask;
@@ -1210,7 +1270,13 @@ ts_status prepare_cone(ts_ctx *c, PlanEntry *pe, int dtype)
     }
     for (int q = 0; q < n; ++q)
         if (pos[q] != q) return fail(TS_EINVAL, "internal: light-cone plan does not restore the layout");
-    ts_status st = alloc(pe->cone_dev, args.size() * sizeof(tsk::ConeArgs));
+    ts_status st = upload_cone_tabs(c, up);
+    if (st != TS_OK) return st;
+    for (const auto &s : steps) {
+        s.first->wgf = s.second->wgf;
+        s.first->dtab = s.second->dtab;
+    }
+    st = alloc(pe->cone_dev, args.size() * sizeof(tsk::ConeArgs));
     if (st != TS_OK) return st;
     TS_HIP(hipMemcpy(pe->cone_dev.p, args.data(), args.size() * sizeof(tsk::ConeArgs), hipMemcpyHostToDevice));
     pe->cone_host.swap(args);

@@ -104,5 +104,11 @@ def tuner_launches(h, dtype):
     return {"cone": h.launches("cone_kernel")}
 
 
+def first_call(h, n, dtype, steps):
+    h.rt.host_reset()
+    h.evolve(h.system(n), dtype, steps)
+    return {"allocs": h.rt.host_allocs(), "uploads": h.rt.host_uploads(), "sweeps": h.launches("cone_kernel")}
+
+
 if __name__ == "__main__":
     print(json.dumps(globals()[sys.argv[1]](Host(), *json.loads(sys.argv[2]))))
