@@ -1457,13 +1457,16 @@ __device__ __forceinline__ void cone_warm(const ConeArgs *__restrict__ a, uint64
     asm volatile("" ::"s"(acc));
 }
 
+// The forms of the light-cone kernel (below).
+constexpr int kConeMany = 0, kConeMid = 1, kConeFew = 2;
+
 // Light-cone sweep.  The same register windows, transposes and phase arithmetic as the
 // register-window sweep, with many phase steps per pass (each restricted to the terms that
 // the host assigned to it, with its own workgroup row and tables) and separate tile-bit maps
 // for the load and the store.  L is the LDS element of the transposes (double: the half
-// buffer for complex128; FEW: a full buffer, or two).  The workgroup row and the window table of a
+// buffer for complex128; KIND kConeFew: a full buffer, or two).  The workgroup row and the window table of a
 // phase step are the same for every lane: the step reads them with scalar loads where it uses them.
-template <typename R, int T, int RB, typename L, bool REC = false, bool FEW = false>
+template <typename R, int T, int RB, typename L, bool REC = false, int KIND = kConeMany>
 __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
                                            const ConeArgs *__restrict__ a, uint64_t tile, L *lds,
                                            const ConeRec *rec = nullptr, double *red = nullptr)
@@ -1484,7 +1487,7 @@ __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
     __builtin_amdgcn_s_waitcnt(0x0F70);
     int cur = a->load_win, half = 0;
     auto transpose = [&](int to) {
-        if constexpr (FEW && cone_two_buffers<T, L>()) {
+        if constexpr (KIND == kConeFew && cone_two_buffers<T, L>()) {
             cone_transpose_next<RB>(x, lds + half, cur, to);
             half = cone_buffer(T) - half;
         } else {
@@ -1499,7 +1502,7 @@ __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
         const int p = (int)((code >> 9) & 63u);
         // the thread's phase-table row is loaded first: its latency then hides behind the
         // transpose and the butterflies of the stage
-        constexpr bool MASKS = sizeof(R) == 4 && !FEW;
+        constexpr bool MASKS = sizeof(R) == 4 && KIND == kConeMany;
         double2 th[MASKS ? 1 + RB : 3];
         gtab row = nullptr;
         if (has_phase) {
@@ -1530,7 +1533,7 @@ __device__ __forceinline__ void cone_sweep(typename Vec<R>::T *__restrict__ psi,
                 default: cone_diag_walk<T, RB>(x, wp, w0, qp, th, ph.xmask, w); break;
                 }
             } else {
-                cone_diag<T, RB, FEW>(x, wp, w0, qp, th, ph.cmask, ph.xmask, row, w);
+                cone_diag<T, RB, KIND != kConeMany>(x, wp, w0, qp, th, ph.cmask, ph.xmask, row, w);
             }
         }
     }
@@ -1553,44 +1556,49 @@ __host__ __device__ constexpr size_t cone_tab_bytes(int n_phases)
 }
 
 // complex128 transposes through the half buffer, so that four workgroups share a CU (four waves
-// per SIMD, as complex64 with its full buffer).  FEW: a launch of at most kConeFewTiles
-// workgroups leaves each CU one of them; its time is the latency of the chain of stages, which a
-// full buffer, or two (one barrier per transpose), and more registers shorten.  It stays within
-// half a CU all the same (registers too: the bound on waves per SIMD), so that launches on other
-// streams run beside it: at kConeFewTiles and four streams (the hardware queues of a process)
-// every workgroup still finds a place at once.
-// Eight fourth-order steps of a complex128 chain, us, this form against the other: N = 18 1140
-// and 1266, N = 19 1205 and 1336 (four streams at once 2730 and 3100); N = 20, 256 workgroups,
-// 1353 and 1500 alone but 3100 and 2300 on four streams.  Two full buffers in complex128 (139 KB,
-// one workgroup per CU) took 1209 at N = 19 and 3220 on four streams.
-template <typename R, bool FEW>
-using ConeLds = typename std::conditional<sizeof(R) == 8, typename std::conditional<FEW, double2, double>::type, float2>::type;
-template <typename R, int T, bool FEW>
+// per SIMD, as complex64 with its full buffer).  A launch of few workgroups leaves each CU one of
+// them; its time is the latency of the chain of stages, which more registers (the phase products
+// of a step all at once) and a full buffer, or two (one barrier per transpose), shorten.  But
+// launches on other streams should run beside it, up to four (the hardware queues of a process):
+// kConeFew, of at most half as many workgroups as CUs, stays within half a CU; kConeMid (complex128,
+// up to one workgroup per CU) keeps the half buffer and three waves per SIMD.
+// Eight fourth-order steps of a complex128 chain, us: N = 18 1140 as kConeFew and 1266 otherwise,
+// N = 19 1205 and 1336 (four streams at once 2730 and 3100); N = 20 as kConeMid 1465 (2290
+// on four streams), as kConeMany 1500 (2300), as kConeFew 1353 (3100).  Two full buffers in
+// complex128 (139 KB, one workgroup per CU) took 1209 at N = 19 and 3220 on four streams.
+template <typename R, int KIND>
+using ConeLds = typename std::conditional<
+    sizeof(R) == 8, typename std::conditional<KIND == kConeFew, double2, double>::type, float2>::type;
+template <typename R, int T, int KIND>
 __host__ __device__ constexpr int cone_lds()
 {
-    return FEW && cone_two_buffers<T, ConeLds<R, FEW>>() ? 2 * cone_buffer(T) : cone_buffer(T);
+    return KIND == kConeFew && cone_two_buffers<T, ConeLds<R, KIND>>() ? 2 * cone_buffer(T) : cone_buffer(T);
 }
-template <typename R, int T, int RB, bool FEW>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(FEW ? T - 10 : 4)))
+__host__ __device__ constexpr int cone_waves(int T, int kind, int many)
+{
+    return kind == kConeFew ? T - 10 : kind == kConeMid ? 3 : many;
+}
+template <typename R, int T, int RB, int KIND>
+__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(cone_waves(T, KIND, 4))))
 void cone_kernel(typename Vec<R>::T *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
                  int reverse)
 {
-    __shared__ ConeLds<R, FEW> lds[cone_lds<R, T, FEW>()];
+    __shared__ ConeLds<R, KIND> lds[cone_lds<R, T, KIND>()];
     const uint64_t tile = reverse ? n_tiles - 1 - blockIdx.x : blockIdx.x;
-    cone_sweep<R, T, RB, ConeLds<R, FEW>, false, FEW>(psi, a, tile, lds);
+    cone_sweep<R, T, RB, ConeLds<R, KIND>, false, KIND>(psi, a, tile, lds);
 }
 
 // The last sweep of a vector's recorded segment, with the segment's observables (at four waves per
 // SIMD its registers would spill; complex64 N = 21 511 against 527 us per two recorded steps).
-template <typename R, int T, int RB, bool FEW>
-__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(FEW ? T - 10 : 3)))
+template <typename R, int T, int RB, int KIND>
+__global__ __launch_bounds__(1 << (T - RB)) __attribute__((amdgpu_waves_per_eu(cone_waves(T, KIND, 3))))
 void cone_rec_kernel(typename Vec<R>::T *__restrict__ psi, const ConeArgs *__restrict__ a, uint64_t n_tiles,
                      int reverse, ConeRec rec)
 {
-    __shared__ ConeLds<R, FEW> lds[cone_lds<R, T, FEW>()];
+    __shared__ ConeLds<R, KIND> lds[cone_lds<R, T, KIND>()];
     __shared__ double red[2 << (T - RB - 6)];
     const uint64_t tile = reverse ? n_tiles - 1 - blockIdx.x : blockIdx.x;
-    cone_sweep<R, T, RB, ConeLds<R, FEW>, true, FEW>(psi, a, tile, lds, &rec, red);
+    cone_sweep<R, T, RB, ConeLds<R, KIND>, true, KIND>(psi, a, tile, lds, &rec, red);
 }
 
 // ------------------------------------------------------------ adjoint light-cone sweep
@@ -3199,23 +3207,26 @@ hipError_t launch_sweep_pair(int dtype, int T, int RB, void *psi, void *lam, con
     return hipErrorInvalidValue;
 }
 
+template <typename R, int T, int KIND>
+static hipError_t launch_cone_k(typename Vec<R>::T *psi, const ConeArgs *a, uint64_t n_tiles, int reverse,
+                                const ConeRec *rec, hipStream_t s)
+{
+    const dim3 grid((uint32_t)n_tiles), block(1 << (T - 4));
+    if (rec)
+        hipLaunchKernelGGL((cone_rec_kernel<R, T, 4, KIND>), grid, block, 0, s, psi, a, n_tiles, reverse, *rec);
+    else
+        hipLaunchKernelGGL((cone_kernel<R, T, 4, KIND>), grid, block, 0, s, psi, a, n_tiles, reverse);
+    return hipGetLastError();
+}
+
 template <typename R, int T>
 static hipError_t launch_cone_t(typename Vec<R>::T *psi, const ConeArgs *a, uint64_t n_tiles, int reverse,
                                 const ConeRec *rec, hipStream_t s)
 {
-    const dim3 grid((uint32_t)n_tiles), block(1 << (T - 4));
-    if (n_tiles <= kConeFewTiles) {
-        if (rec)
-            hipLaunchKernelGGL((cone_rec_kernel<R, T, 4, true>), grid, block, 0, s, psi, a, n_tiles, reverse, *rec);
-        else
-            hipLaunchKernelGGL((cone_kernel<R, T, 4, true>), grid, block, 0, s, psi, a, n_tiles, reverse);
-        return hipGetLastError();
-    }
-    if (rec)
-        hipLaunchKernelGGL((cone_rec_kernel<R, T, 4, false>), grid, block, 0, s, psi, a, n_tiles, reverse, *rec);
-    else
-        hipLaunchKernelGGL((cone_kernel<R, T, 4, false>), grid, block, 0, s, psi, a, n_tiles, reverse);
-    return hipGetLastError();
+    if (n_tiles <= kConeFewTiles) return launch_cone_k<R, T, kConeFew>(psi, a, n_tiles, reverse, rec, s);
+    if constexpr (sizeof(R) == 8)
+        if (n_tiles <= kConeMidTiles) return launch_cone_k<R, T, kConeMid>(psi, a, n_tiles, reverse, rec, s);
+    return launch_cone_k<R, T, kConeMany>(psi, a, n_tiles, reverse, rec, s);
 }
 
 static hipError_t launch_cone_any(int dtype, int T, int RB, void *psi, const ConeArgs *a, int n_phases,

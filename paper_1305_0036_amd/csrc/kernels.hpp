@@ -410,10 +410,11 @@ hipError_t launch_cone_pair(int dtype, int T, int RB, void *psi, void *lam, cons
                             const ConeGradArgs *g, int n_slots, double *slots, int stride, uint64_t n_tiles,
                             int reverse, hipStream_t s);
 
-// Launches of at most this many workgroups run the light-cone kernel that takes half a CU per
-// workgroup (two fit), larger ones the one of four workgroups per CU.  Half the CUs: a second
-// and a third launch of that size on other streams then still run beside the first.
-constexpr uint64_t kConeFewTiles = 128;
+// Launches of at most kConeFewTiles workgroups (half the CUs: a second and a third launch of that
+// size on other streams then still run beside the first) run the form of the light-cone kernel that
+// takes half a CU per workgroup; complex128 ones of at most kConeMidTiles (one per CU) the form of
+// three workgroups per CU; larger ones that of four.
+constexpr uint64_t kConeFewTiles = 128, kConeMidTiles = 256;
 // One light-cone sweep of n_tiles workgroups; `a` points to device memory and n_phases is its
 // n_phases (checked against the limit).  The phase tables that `a` names are read-only while
 // the sweep runs (the kernel reads them through the scalar data cache).
