@@ -354,11 +354,22 @@ bool cone_stages(const ts::ConeSweep &sw, int T, int RB, int s, tsk::ConeArgs &a
                  std::vector<int> &phase_win, int *transposes);
 
 // The model's time (us) of a light-cone plan's sweeps, or a negative number where the kernel cannot
-// run them.
-double cone_cost(const ts_ctx *c, const ts::ConePlan &cp, int dtype)
+// run them.  A plan that reaches `bound` before its transposes are counted is given as it stands
+// (choosing the stages takes most of the planning).
+double cone_cost(const ts_ctx *c, const ts::ConePlan &cp, int dtype, double bound)
 {
     const int T = cp.T;
+    const bool c128 = dtype == TS_C128;
+    const double scale = std::ldexp(1.0, c->n - 27);
     double cost = 0.0;
+    for (const ts::ConeSweep &sw : cp.sweeps) {
+        int sl = 0;
+        for (const ts::ConeOp &op : sw.ops)
+            if (op.kind == 0) sl += __builtin_popcountll(op.spins);
+        const double ph = (double)sw.phases.size();
+        cost += (c128 ? 526.0 + 40.1 * ph + 11.3 * sl : 201.0 + 41.5 * ph + 11.9 * sl) * scale + kLaunchUs;
+    }
+    if (cost >= bound) return cost;
     for (const ts::ConeSweep &sw : cp.sweeps) {
         tsk::ConeArgs a;
         std::vector<int> pw;
@@ -377,14 +388,9 @@ double cone_cost(const ts_ctx *c, const ts::ConePlan &cp, int dtype)
             }
             if (__builtin_popcountll(outside) > tsk::kConeRowBits) return -1.0;
         }
-        int sl = 0;
-        for (const ts::ConeOp &op : sw.ops)
-            if (op.kind == 0) sl += __builtin_popcountll(op.spins);
-        const double ph = (double)sw.phases.size();
-        cost += dtype == TS_C128 ? 526.0 + 30.3 * tr + 40.1 * ph + 11.3 * sl
-                                 : 201.0 + 8.3 * tr + 41.5 * ph + 11.9 * sl;
+        cost += (c128 ? 30.3 : 8.3) * tr * scale;
     }
-    return cost * std::ldexp(1.0, c->n - 27) + kLaunchUs * (double)cp.sweeps.size();
+    return cost;
 }
 
 // Light-cone plan of a chain, with the windows packed from the left or (complex128) spread evenly.
@@ -395,9 +401,10 @@ double cone_cost(const ts_ctx *c, const ts::ConePlan &cp, int dtype)
 // N = 23 next-nearest bonds 0.82 (model 0.86), N = 26 a three-wide ladder 1.07 (1.08), N = 29 a
 // chain, first order, 1.19 (1.08).  complex64 keeps the packed windows: its roundings depend on
 // which sweep takes which layer, and its results stay what they were.  even: -1 as the model says,
-// else 0 or 1; the choice comes back in it.  *cost < 0: a plan, but none that the kernel can run.
+// else 0 or 1; the choice comes back in it.  *cost < 0: a plan, but none that the kernel can run;
+// >= bound: none that is cheaper.
 bool cone_windows(const ts_ctx *c, const ts::FoldedChain &chain, int T, int s, int dtype, int max_adv,
-                  size_t limit, int *even, ts::ConePlan &out, double *cost)
+                  size_t limit, double bound, int *even, ts::ConePlan &out, double *cost)
 {
     std::vector<std::pair<int, int>> bonds;
     for (size_t k = 0; k < c->bi.size(); ++k) bonds.push_back({c->bi[k], c->bj[k]});
@@ -405,10 +412,12 @@ bool cone_windows(const ts_ctx *c, const ts::FoldedChain &chain, int T, int s, i
     *even = -1;
     for (int w = 0; w < 2; ++w) {
         if (want >= 0 && w != want) continue;
+        if (w == 1 && c->n <= 2 * T - s) continue;   // two windows: there is nothing to spread
         ts::ConePlan cp;
         if (!ts::make_cone_plan(chain, c->n, T, s, bonds, max_adv, limit, cp, tsk::kConePhases, w == 1)) continue;
-        const double t = cone_cost(c, cp, dtype);
-        if (*even >= 0 && (t < 0.0 || (*cost >= 0.0 && t >= 0.985 * *cost))) continue;
+        const bool better = *even >= 0 && *cost >= 0.0;   // only then there is a plan to beat
+        const double t = cone_cost(c, cp, dtype, better ? std::min(bound, 0.985 * *cost) : bound);
+        if (*even >= 0 && (t < 0.0 || (better && t >= 0.985 * *cost))) continue;
         *even = w;
         *cost = t;
         out = std::move(cp);
@@ -423,15 +432,34 @@ bool cone_candidate(ts_ctx *c, PlanEntry *pe, int T, int dtype, int mode, const 
     double cost;
     int even = like ? like->cone_even : -1;
     const size_t limit = 4 * pe->plan.sweeps.size() + 16;
-    if (!cone_windows(c, pe->plan.chain, T, kConeLowBits, dtype, c->cone_adv, limit, &even, cp, &cost) || cost < 0.0)
-        return false;  // keep the ping-pong plan
     const double pp = (double)pe->plan.sweeps.size() * pingpong_sweep_us(dtype, T);
     const double ppc = pp * std::ldexp(1.0, c->n - 27) + kLaunchUs * (double)pe->plan.sweeps.size();
-    if (mode == 1 && cost >= 0.95 * ppc) return false;
+    const double bound = mode == 1 ? 0.95 * ppc : HUGE_VAL;
+    if (!cone_windows(c, pe->plan.chain, T, kConeLowBits, dtype, c->cone_adv, limit, bound, &even, cp, &cost) ||
+        cost < 0.0 || cost >= bound)
+        return false;  // keep the ping-pong plan
     pe->cone_plan = std::move(cp);
     pe->cone_cost = cost;
     pe->cone_even = even;
     return true;
+}
+
+// Narrow tiles: complex128 states of at most kNarrowSpins spins, neither tuned nor configured,
+// leave most CUs idle at the default width (2^(n - 12) workgroups, at most 128 up to n = 19), and
+// a sweep is the latency of one workgroup.  See resolve_tile for the widths and what they measured.
+// complex64 keeps the default: its roundings depend on the tiles, and its results stay what
+// they were.
+constexpr int kNarrowSpins = 19;
+bool narrow_tiles(const ts_ctx *c, int dtype)
+{
+    return dtype == TS_C128 && c->tile_bits[dtype] == 0 && c->reg_bits[dtype] == 4 && c->sweep_variant[dtype] == 4 &&
+           c->n > default_tile_bits(dtype) && c->n <= kNarrowSpins;
+}
+// Amplitudes per thread (2^RB) of the ping-pong sweeps at width T: narrow tiles halve them, which
+// gives the SIMDs of a CU twice the waves.
+int sweep_reg_bits(const ts_ctx *c, int dtype, int T)
+{
+    return narrow_tiles(c, dtype) && T < default_tile_bits(dtype) ? 3 : c->reg_bits[dtype];
 }
 
 // adjoint = true: keep the partial evolutions of vanishing axes (their parameters still
@@ -443,11 +471,12 @@ ts_status build_plan(ts_ctx *c, int dtype, int T, int order, double dt, int64_t 
 {
     uint64_t dtb;
     std::memcpy(&dtb, &dt, sizeof dtb);
-    // the light-cone form depends on the context's kernel configuration, which tuning changes: a
-    // plan made under another one is another plan
-    const int cm = adjoint || c->reg_bits[dtype] != 4 || (T != 11 && T != 12) ? 0
-                   : c->cone_mode >= 0                                        ? c->cone_mode
-                                                                              : c->sweep_variant[dtype] == 4;
+    // the light-cone form (not looked for at a narrow width, which is for ping-pong sweeps) depends
+    // on the context's kernel configuration, which tuning changes: a plan made under another one
+    // is another plan
+    const int cm = adjoint || sweep_reg_bits(c, dtype, T) != 4 || (T != 11 && T != 12) ? 0
+                   : c->cone_mode >= 0                                                 ? c->cone_mode
+                                                                       : c->sweep_variant[dtype] == 4;
     auto key = std::make_tuple(dtype + (adjoint ? (split ? 2 : 4) : 0) + 8 * cm, T, order, dtb, nsteps);
     auto it = c->plans.find(key);
     if (it != c->plans.end()) {
@@ -468,24 +497,6 @@ ts_status build_plan(ts_ctx *c, int dtype, int T, int order, double dt, int64_t 
     *out = pe.get();
     c->plans.emplace(key, std::move(pe));
     return TS_OK;
-}
-
-// Narrow tiles: complex128 states of at most kNarrowSpins spins, neither tuned nor configured,
-// leave most CUs idle at the default width (2^(n - 12) workgroups, at most 128 up to n = 19), and
-// a sweep is the latency of one workgroup.  See resolve_tile for the widths and what they measured.
-// complex64 keeps the default: its roundings depend on the tiles, and its results stay what
-// they were.
-constexpr int kNarrowSpins = 19;
-bool narrow_tiles(const ts_ctx *c, int dtype)
-{
-    return dtype == TS_C128 && c->tile_bits[dtype] == 0 && c->reg_bits[dtype] == 4 && c->sweep_variant[dtype] == 4 &&
-           c->n > default_tile_bits(dtype) && c->n <= kNarrowSpins;
-}
-// Amplitudes per thread (2^RB) of the ping-pong sweeps at width T: narrow tiles halve them, which
-// gives the SIMDs of a CU twice the waves.
-int sweep_reg_bits(const ts_ctx *c, int dtype, int T)
-{
-    return narrow_tiles(c, dtype) && T < default_tile_bits(dtype) ? 3 : c->reg_bits[dtype];
 }
 
 // Tile width of ts_evolve when the caller fixed none.  The default (12) keeps every tile
@@ -2867,7 +2878,7 @@ ts_status ts_cone_describe(ts_ctx *ctx, ts_dtype dtype, double dt, int64_t nstep
     }
     double cost;
     int even = -1;
-    if (!cone_windows(ctx, P.chain, T, s, dtype, max_adv, 1u << 20, &even, cp, &cost))
+    if (!cone_windows(ctx, P.chain, T, s, dtype, max_adv, 1u << 20, HUGE_VAL, &even, cp, &cost))
         return fail(TS_EINVAL, "no light-cone plan for these sizes");
     if (used) {
         *used = 0;

@@ -8,6 +8,7 @@ import json
 import os
 import subprocess
 import sys
+import time
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 LIB = os.path.join(ROOT, "paper_1305_0036_amd", "libtsspin.so")
@@ -108,6 +109,20 @@ def first_call(h, n, dtype, steps):
     h.rt.host_reset()
     h.evolve(h.system(n), dtype, steps)
     return {"allocs": h.rt.host_allocs(), "uploads": h.rt.host_uploads(), "sweeps": h.launches("cone_kernel")}
+
+
+def narrow_first_call(h, n):
+    """Least time of the first call of a ring at its own width over that at width 12."""
+    best = {0: 1e9, 12: 1e9}
+    for _ in range(25):
+        for width in best:
+            ctx = h.system(n, ring=True)
+            h.ok(h.lib.ts_set_tile_bits(ctx, C128, width))
+            t = time.perf_counter()
+            h.evolve(ctx, C128, 8)
+            best[width] = min(best[width], time.perf_counter() - t)
+            h.ok(h.lib.ts_destroy(ctx))
+    return {"ratio": best[0] / best[12]}
 
 
 if __name__ == "__main__":
