@@ -18,6 +18,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <set>
 #include <stdexcept>
 #include <string>
 #include <tuple>
@@ -101,6 +102,11 @@ struct PlanEntry {
     bool etab_prepared = false, etab_ok = false;
 };
 
+// Phase tables of resident chains that a batch keeps over all its programs, and the most and the
+// least that a group of chains of a class that does not fit has.
+constexpr size_t kResidentTabBytes = (size_t)4 << 30;
+constexpr size_t kResidentGroupMax = (size_t)1 << 30, kResidentGroupMin = (size_t)256 << 20;
+
 // Phase factors of one light-cone phase step (restricted terms): workgroup rows and the
 // per-thread / window table.
 struct ConeTab {
@@ -183,6 +189,9 @@ struct ts_ctx {
     DevBuf energy_ops[2];
     // batch context: one sub-context per chain (empty for a single system)
     std::vector<std::unique_ptr<ts_ctx>> chains;
+    // phase tables of whole classes of resident chains, shared by the programs that need the same
+    std::map<std::string, std::weak_ptr<DevBuf>> resident_tabs;
+    size_t resident_tab_bytes = kResidentTabBytes;   // $TSSPIN_RESIDENT_TAB_BYTES
     std::map<std::string, std::unique_ptr<struct BatchProgram>> programs;
     std::vector<std::string> program_order;     // keys of `programs`, least recently used first
     int64_t graph_replays = 0, eager_runs = 0, capture_failures = 0;
@@ -1573,9 +1582,6 @@ ts_status resident_args(ts_ctx *c, PlanEntry *pe, int dtype, tsk::ResidentArgs *
     return TS_OK;
 }
 
-// Phase tables that a batch keeps for one class of resident chains.
-constexpr size_t kResidentTabBytes = (size_t)1 << 30;
-
 // Segments one recorded resident launch runs at most.
 constexpr int64_t kResidentReps = 4096;
 
@@ -2120,6 +2126,7 @@ struct BatchProgram {
     int dtype = 0;
     std::vector<std::vector<BatchLaunch>> per_class;
     std::vector<std::unique_ptr<DevBuf>> bufs;
+    std::vector<std::shared_ptr<DevBuf>> tabs;   // phase tables of its resident classes
     std::vector<hipStream_t> streams;
     std::vector<hipEvent_t> events;   // [0] fork, [1] entry from the caller, then one join per class
     hipStream_t cap = nullptr;        // capture stream
@@ -2162,6 +2169,48 @@ hipError_t run_launch(int dtype, const BatchLaunch &L, hipStream_t s)
                                       L.reverse, s);
     default: return tsk::launch_batch_reduce(dtype, L.ba, (int)L.count, L.partials, L.nbpc, s);
     }
+}
+
+// Buffer for the phase tables of a resident class.  They outgrow the states (order 4, every axis:
+// 81 KB per chain at 10 spins, 329 KB at 12; complex64 160 and 640 KB), so a batch keeps at most
+// resident_tab_bytes of them over all its programs.  A class that fits has them filled once (*group:
+// all its chains), and programs with the same phase steps share them; any other runs in groups of
+// chains that share a buffer of the program, each filling it anew (*group chains of it).  2000
+// complex64 chains of 12 spins (1.3 GB), us for one step and for four: 598 and 2015 kept, 970 and
+// 2520 in groups of 1 GiB, 1020 and 2760 in groups of 256 MB; with the phases formed where they
+// are used, in LDS, 940 and 3540.  A buffer that the device has no room for is tried at half the
+// size.
+ts_status resident_tables(ts_ctx *ctx, BatchProgram *bp, const std::string &key, size_t chains, size_t per_chain,
+                          std::shared_ptr<DevBuf> *tab, size_t *group, bool *filled)
+{
+    *filled = false;
+    for (auto t = ctx->resident_tabs.begin(); t != ctx->resident_tabs.end();)   // of programs dropped since
+        t = t->second.expired() ? ctx->resident_tabs.erase(t) : std::next(t);
+    auto it = ctx->resident_tabs.find(key);
+    if (it != ctx->resident_tabs.end() && (*tab = it->second.lock())) {
+        *group = chains;
+        *filled = true;
+        return TS_OK;
+    }
+    std::set<const DevBuf *> live;
+    for (const auto &p : ctx->programs)
+        for (const auto &t : p.second->tabs) live.insert(t.get());
+    for (const auto &t : bp->tabs) live.insert(t.get());
+    size_t held = 0;
+    for (const DevBuf *t : live) held += t->bytes;
+    const size_t room = ctx->resident_tab_bytes - std::min(held, ctx->resident_tab_bytes);
+    *group = std::min<size_t>(65535, chains);
+    if (*group < chains || *group * per_chain > room) {
+        const size_t bytes = std::max(kResidentGroupMin, std::min(kResidentGroupMax, room));
+        *group = std::min(*group, std::max<size_t>(1, std::min(bytes, ctx->resident_tab_bytes) / per_chain));
+    }
+    *tab = std::make_shared<DevBuf>();
+    ts_status st;
+    while ((st = alloc(**tab, *group * per_chain)) == TS_ENOMEM && *group > 1) {
+        (void)hipGetLastError();
+        *group = (*group + 1) / 2;
+    }
+    return st;
 }
 
 // Build the launches of one batched evolution (all tables and device arrays are uploaded
@@ -2232,16 +2281,18 @@ ts_status build_batch_program(ts_ctx *ctx, char *psi_packed, const int64_t *psi_
                 }
                 rc.push_back(x);
             }
-            // The phase tables of a class of many chains outgrow its states (about 60 KB per
-            // chain at 10 spins, 250 KB at 12; complex64 600 KB): at most kResidentTabBytes of them are kept.
-            // A class that fits has them filled once, here; a larger one runs in groups of
-            // chains that share the buffer, each filling it anew.
             const size_t per_chain = phases.size() * sizeof(double2) *
                                      (tsk::resident_ascending(dtype) ? (size_t)1 << n : tsk::resident_phase_entries(n));
-            const size_t group = std::min<size_t>(mem.size(),
-                                                  std::min<size_t>(65535, std::max<size_t>(1, kResidentTabBytes / per_chain)));
-            auto tb = std::make_unique<DevBuf>();
-            st = alloc(*tb, group * per_chain);
+            std::string tkey = std::to_string(kv.first) + "/" + std::to_string(dtype);
+            for (const tsk::ResidentPhase &ph : phases) {
+                const double f[] = {ph.d.tau, ph.d.kre, ph.d.kim};
+                tkey += "/" + std::to_string(ph.d.axis) + "," + std::to_string(ph.d.qturn) + "," + std::to_string(ph.top);
+                tkey.append(reinterpret_cast<const char *>(f), sizeof f);
+            }
+            bool filled;
+            size_t group;
+            std::shared_ptr<DevBuf> tb;
+            st = resident_tables(ctx, bp, tkey, mem.size(), per_chain, &tb, &group, &filled);
             if (st != TS_OK) return st;
             BatchLaunch bl, fill;
             bl.kind = 0;
@@ -2259,18 +2310,19 @@ ts_status build_batch_program(ts_ctx *ctx, char *psi_packed, const int64_t *psi_
             for (size_t o = 0; o < obs.size(); ++o) bl.ra.obs[o] = obs[o];
             bl.ra.n_obs = (int)obs.size();
             bl.ra.slots = slots;
-            bp->bufs.push_back(std::move(tb));
+            bp->tabs.push_back(tb);
             const tsk::ResidentChain *all = bl.ra.chains;
             for (size_t g = 0; g < mem.size(); g += group) {
                 bl.ra.chains = fill.pa.chains = all + g;
                 bl.count = fill.count = (uint32_t)std::min(group, mem.size() - g);
                 if (group < mem.size())
                     L.push_back(fill);
-                else
+                else if (!filled)
                     TS_HIP(tsk::launch_resident_phases(dtype, fill.pa, (int)fill.count, nullptr));
                 L.push_back(bl);
             }
             TS_HIP(hipStreamSynchronize(nullptr));
+            if (group == mem.size()) ctx->resident_tabs[tkey] = tb;
             bp->per_class.push_back(std::move(L));
             continue;
         }
@@ -3468,6 +3520,7 @@ extern "C" ts_status ts_create_batch(int32_t n_chains, const int32_t *n_spins, c
     // instructions, measured slower on the 512-chain workload
     b->cone_mode = 0;
     if (const char *v = std::getenv("TSSPIN_CONE")) b->cone_mode = std::atoi(v);
+    if (const char *v = std::getenv("TSSPIN_RESIDENT_TAB_BYTES")) b->resident_tab_bytes = (size_t)std::strtoull(v, nullptr, 10);
     *out = b.release();
     return TS_OK;
 }

@@ -125,5 +125,36 @@ def narrow_first_call(h, n):
     return {"ratio": best[0] / best[12]}
 
 
+def batch_tables(h, n, chains, dtype, dts, pointers):
+    """Device bytes held after each call of a batch: every time step at every state pointer."""
+    ctx, ns, held = h.batch([n] * chains), [n] * chains, []
+    for dt in dts:
+        for at in pointers:
+            h.ok(h.evolve_batch(ctx, ns, dtype, 1, dt=dt, at=at))
+            held.append(h.rt.host_held())
+    return held
+
+
+def batch_groups(h, n, chains, dtype):
+    """Launches of one call's program (they are captured once) and their fills."""
+    ctx, ns = h.batch([n] * chains), [n] * chains
+    h.rt.host_reset()
+    h.ok(h.evolve_batch(ctx, ns, dtype, 1))
+    fills = h.launches("resident_phase_kernel") + h.launches("resident_diag_kernel")
+    return {"fills": fills, "runs": h.launches("15resident_kernel")}
+
+
+def batch_short_of_memory(h, n, chains, dtype, spare):
+    """A first call with `spare` bytes less than it would like."""
+    ctx, ns = h.batch([n] * chains), [n] * chains
+    h.ok(h.evolve_batch(ctx, ns, dtype, 1, dt=0.05))
+    h.ok(h.lib.ts_destroy(ctx))
+    need = h.rt.host_peak()
+    ctx = h.batch(ns)
+    h.rt.host_limit(C.c_size_t(need - spare))
+    rc = h.evolve_batch(ctx, ns, dtype, 1, dt=0.05)
+    return {"rc": rc, "failed": h.rt.host_failed()}
+
+
 if __name__ == "__main__":
     print(json.dumps(globals()[sys.argv[1]](Host(), *json.loads(sys.argv[2]))))
