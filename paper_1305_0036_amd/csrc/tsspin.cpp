@@ -170,6 +170,7 @@ struct ts_ctx {
     DevBuf cone_partials;  // observables folded into light-cone sweeps: [workgroups][2 * kMaxObs]
     int64_t cone_partial_rows = 0;   // workgroups of the last sweep that wrote them
     bool no_fuse = false;  // $TSSPIN_NO_FUSE: records always by separate reductions
+    bool res_fac = true;   // $TSSPIN_RESIDENT_FACTORS=0: complex128 resident states form their phases in the kernel
     bool adj_split = false;  // $TSSPIN_ADJ_SPLIT: the adjoint's split-phase plan and separate gradient passes
     bool adj_cone = true;    // $TSSPIN_ADJ_CONE=0: the adjoint's reverse pass keeps the ping-pong form
     DevBuf expect_out;     // ts_expect staging
@@ -1554,7 +1555,7 @@ ts_status resident_args(ts_ctx *c, PlanEntry *pe, int dtype, tsk::ResidentArgs *
         const bool asc = tsk::resident_ascending(dtype);   // the tables are the factors
         st = alloc(tab, phases.size() * (asc ? (size_t)1 << n : tsk::resident_phase_entries(n)) * sizeof(double2));
         if (st != TS_OK) return st;
-        const bool fac = !asc && n <= tsk::kResidentFactorSpins;
+        const bool fac = !asc && n <= tsk::kResidentFactorSpins && c->res_fac;
         if (fac) st = alloc(pe->resident_fac, (phases.size() << n) * sizeof(double2));
         if (st != TS_OK) return st;
         TS_HIP(hipMemcpy(pe->resident_ops.p, ops.data(), ops.size() * sizeof(tsk::ResidentOp),
@@ -2555,6 +2556,7 @@ ts_status ts_create(int32_t n_spins, const ts_bond *bonds, int32_t n_bonds, cons
     if (const char *v = std::getenv("TSSPIN_CONE")) c->cone_mode = std::atoi(v);
     if (const char *v = std::getenv("TSSPIN_CONE_ADV")) c->cone_adv = std::atoi(v);
     if (const char *v = std::getenv("TSSPIN_NO_FUSE")) c->no_fuse = std::strcmp(v, "0") != 0;
+    if (const char *v = std::getenv("TSSPIN_RESIDENT_FACTORS")) c->res_fac = std::strcmp(v, "0") != 0;
     if (const char *v = std::getenv("TSSPIN_ADJ_SPLIT")) c->adj_split = std::strcmp(v, "0") != 0;
     if (const char *v = std::getenv("TSSPIN_ADJ_CONE")) c->adj_cone = std::strcmp(v, "0") != 0;
     c->h.assign(n_spins, {0.0, 0.0, 0.0});

@@ -156,5 +156,11 @@ def batch_short_of_memory(h, n, chains, dtype, spare):
     return {"rc": rc, "failed": h.rt.host_failed()}
 
 
+def resident_factors(h, n, dtype):
+    """Launches that store the factors of a resident state's phase steps, and of its kernel."""
+    h.evolve(h.system(n), dtype, 3)
+    return {"stored": h.launches("resident_factor_kernel"), "runs": h.launches("15resident_kernel")}
+
+
 if __name__ == "__main__":
     print(json.dumps(globals()[sys.argv[1]](Host(), *json.loads(sys.argv[2]))))
