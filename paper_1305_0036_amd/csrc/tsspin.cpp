@@ -460,10 +460,13 @@ bool cone_candidate(ts_ctx *c, PlanEntry *pe, int T, int dtype, int mode, const 
 // complex64 keeps the default: its roundings depend on the tiles, and its results stay what
 // they were.
 constexpr int kNarrowSpins = 19;
+int narrow_width(int n, int dtype) { return (n + min_run_bits(dtype) + 1) / 2; }
+// Sizes whose untuned complex128 ping-pong sweeps run on narrow tiles.
+bool narrow_size(int dtype, int n) { return dtype == TS_C128 && n > default_tile_bits(dtype) && n <= kNarrowSpins; }
 bool narrow_tiles(const ts_ctx *c, int dtype)
 {
-    return dtype == TS_C128 && c->tile_bits[dtype] == 0 && c->reg_bits[dtype] == 4 && c->sweep_variant[dtype] == 4 &&
-           c->n > default_tile_bits(dtype) && c->n <= kNarrowSpins;
+    return narrow_size(dtype, c->n) && c->tile_bits[dtype] == 0 && c->reg_bits[dtype] == 4 &&
+           c->sweep_variant[dtype] == 4;
 }
 // Amplitudes per thread (2^RB) of the ping-pong sweeps at width T: narrow tiles halve them, which
 // gives the SIMDs of a CU twice the waves.
@@ -532,7 +535,7 @@ ts_status resolve_tile(ts_ctx *c, int dtype, int order, double dt, int64_t nstep
         PlanEntry *p0;
         ts_status st = build_plan(c, dtype, T0, order, dt, nsteps, &p0);
         if (st != TS_OK) return st;
-        if (!p0->cone) *T_out = c->n == T0 + 1 ? c->n : (c->n + min_run_bits(dtype) + 1) / 2;
+        if (!p0->cone) *T_out = c->n == T0 + 1 ? c->n : narrow_width(c->n, dtype);
         return TS_OK;
     }
     auto ngroups = [&](int T) {
@@ -1927,13 +1930,17 @@ bool aligned(const void *p, int dtype) { return ((uintptr_t)p % (dtype == TS_C12
 // The autotuner (ts_autotune) times candidate kernel configurations and stores the fastest
 // per (GPU architecture, spins, dtype, order) in a JSON file:
 //   {"entries": [{"arch": "gfx950", "n": 27, "dtype": 0, "order": 4, "tile_bits": 12,
-//                 "reg_bits": 4, "variant": 0, "ms_per_step": 28.1}, ...]}
-// The reader accepts exactly that shape; anything else reads as an empty cache, so a
-// damaged file only causes re-tuning.
+//                 "reg_bits": 4, "variant": 0, "ms_per_step": 28.1, "kernels": 2}, ...]}
+// The reader accepts exactly that shape ("kernels" may be missing: 1); anything else reads as an
+// empty cache, so a damaged file only causes re-tuning.
+
+// Kernels that an entry was measured with.  2: narrow tiles of small complex128 states; what was
+// measured for such states before them is slower than their default and is not used.
+constexpr int kTuneKernels = 2;
 
 struct TuneEntry {
     std::string arch;
-    int n = 0, dtype = 0, order = 0, tile_bits = 0, reg_bits = 0, variant = 0;
+    int n = 0, dtype = 0, order = 0, tile_bits = 0, reg_bits = 0, variant = 0, kernels = 1;
     double ms = 0.0;
 };
 
@@ -1993,6 +2000,7 @@ bool parse_entry(const std::string &obj, TuneEntry &e)
         else if (key == "reg_bits") { e.reg_bits = (int)v; found |= 32; }
         else if (key == "variant") { e.variant = (int)v; found |= 64; }
         else if (key == "ms_per_step") { e.ms = v; found |= 128; }
+        else if (key == "kernels") e.kernels = (int)v;
     }
     return found == 255;
 }
@@ -2044,8 +2052,9 @@ bool write_tune_cache(const std::string &path, const std::vector<TuneEntry> &es)
         const TuneEntry &e = es[i];
         std::fprintf(f,
                      "%s\n  {\"arch\": \"%s\", \"n\": %d, \"dtype\": %d, \"order\": %d, \"tile_bits\": %d, "
-                     "\"reg_bits\": %d, \"variant\": %d, \"ms_per_step\": %.6g}",
-                     i ? "," : "", e.arch.c_str(), e.n, e.dtype, e.order, e.tile_bits, e.reg_bits, e.variant, e.ms);
+                     "\"reg_bits\": %d, \"variant\": %d, \"ms_per_step\": %.6g, \"kernels\": %d}",
+                     i ? "," : "", e.arch.c_str(), e.n, e.dtype, e.order, e.tile_bits, e.reg_bits, e.variant, e.ms,
+                     e.kernels);
     }
     std::fprintf(f, "\n]}\n");
     const bool ok = std::fclose(f) == 0;
@@ -2062,6 +2071,13 @@ bool valid_config(int dtype, int n, int T, int RB, int variant)
     if (variant != 1 && RB == 3 && T > 13) return false;
     if (variant == 2 && (T < 10 || T > 13 || (T == 13 && (dtype == TS_C128 || RB == 4)))) return false;
     return n >= 1;
+}
+
+bool tune_entry_for(const TuneEntry &e, const std::string &arch, int n, int dtype, int order)
+{
+    return e.arch == arch && e.n == n && e.dtype == dtype && e.order == order &&
+           valid_config(dtype, n, e.tile_bits, e.reg_bits, e.variant) &&
+           (e.kernels >= kTuneKernels || !narrow_size(dtype, n));
 }
 
 // Drop a batch's captured programs.  Each runs its classes on streams of its own, so an event
@@ -2091,8 +2107,7 @@ void consult_tune_cache(ts_ctx *c, int dtype, int order)
     if (std::getenv("TSSPIN_NO_TUNE_CACHE")) return;
     const std::string arch = device_arch();
     for (const TuneEntry &e : read_tune_cache(tune_cache_path()))
-        if (e.arch == arch && e.n == c->n && e.dtype == dtype && e.order == order &&
-            valid_config(dtype, c->n, e.tile_bits, e.reg_bits, e.variant)) {
+        if (tune_entry_for(e, arch, c->n, dtype, order)) {
             apply_config(c, dtype, e.tile_bits, e.reg_bits, e.variant);
             return;
         }
@@ -3418,8 +3433,7 @@ extern "C" ts_status ts_autotune(ts_ctx *ctx, ts_dtype dtype, int32_t order, voi
     std::vector<TuneEntry> cache = read_tune_cache(path);
     if (use_cache) {
         for (const TuneEntry &e : cache)
-            if (e.arch == arch && e.n == ctx->n && e.dtype == dtype && e.order == order &&
-                valid_config(dtype, ctx->n, e.tile_bits, e.reg_bits, e.variant)) {
+            if (tune_entry_for(e, arch, ctx->n, dtype, order)) {
                 apply_config(ctx, dtype, e.tile_bits, e.reg_bits, e.variant);
                 ctx->tune_checked[dtype] = true;
                 if (ms_per_step) *ms_per_step = e.ms;
@@ -3431,6 +3445,10 @@ extern "C" ts_status ts_autotune(ts_ctx *ctx, ts_dtype dtype, int32_t order, voi
     const int hi = dtype == TS_C128 ? 13 : 14;
     struct Cand { int T, RB, v; };
     std::vector<Cand> cands;
+    // (the untuned width where that is narrower; 13 spins run whole in one workgroup)
+    if (const int Tn = narrow_width(ctx->n, dtype);
+        narrow_size(dtype, ctx->n) && ctx->n > default_tile_bits(dtype) + 1 && Tn < 10)
+        cands.push_back({Tn, 3, 0});
     for (int T = 10; T <= hi; ++T) {
         for (int RB = 3; RB <= 4; ++RB)
             for (int v : {0, 2, 3, 4, 5})
@@ -3489,6 +3507,7 @@ extern "C" ts_status ts_autotune(ts_ctx *ctx, ts_dtype dtype, int32_t order, voi
     ne.reg_bits = bc.RB;
     ne.variant = bc.v;
     ne.ms = best;
+    ne.kernels = kTuneKernels;
     out.push_back(ne);
     (void)write_tune_cache(path, out);  // a cache that cannot be written only costs re-tuning
     return TS_OK;

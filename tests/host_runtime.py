@@ -162,5 +162,14 @@ def resident_factors(h, n, dtype):
     return {"stored": h.launches("resident_factor_kernel"), "runs": h.launches("15resident_kernel")}
 
 
+def tuner_widths(h, n, dtype):
+    """Launches of the narrow untuned width in a tuning, and the kernel configuration before it."""
+    ctx, cfg = h.system(n, ring=True), [C.c_int32() for _ in range(3)]
+    h.ok(h.lib.ts_get_kernel_config(ctx, dtype, 4, *[C.byref(c) for c in cfg]))
+    h.rt.host_reset()
+    h.autotune(ctx, dtype, 0)
+    return {"untuned": [c.value for c in cfg[:2]], "timed": h.launches(f"sweep_reg_kernelIdLi{cfg[0].value}ELi{cfg[1].value}E")}
+
+
 if __name__ == "__main__":
     print(json.dumps(globals()[sys.argv[1]](Host(), *json.loads(sys.argv[2]))))
