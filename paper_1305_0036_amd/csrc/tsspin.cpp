@@ -118,18 +118,22 @@ struct ConeTab {
     uint32_t cmask = 0;   // window bits with a thread- or workgroup-dependent walk factor
 };
 
-// Tables on their way to the device: formed in a host buffer, and uploaded a megabyte at a time.  A
+// Tables on their way to the device: formed in a host buffer, and uploaded two megabytes at a time.  A
 // plan can need some hundred (125 to 275 for eight steps of a chain of 23 spins), and two
 // allocations and two blocking copies for each took as long as forming them.
 struct ConeUpload {
-    static constexpr size_t kBytes = (size_t)1 << 20;
+    static constexpr size_t kBytes = (size_t)2 << 20;
+    // Tables start at pages, as those of an allocation each do: at multiples of 256 bytes eight
+    // complex128 steps of 16 spins with next-nearest bonds took 990 us instead of 937 (which cache
+    // lines the steps' scalar loads share), of 64 KB 1093.
+    static constexpr size_t kAlign = 4096 / sizeof(ts::cplx);
     std::vector<ts::cplx> host;
     std::map<std::string, std::unique_ptr<ConeTab>> tabs;
-    // room for a table, at a multiple of 256 bytes
+    // room for a table
     size_t add(size_t entries)
     {
         if (host.empty()) host.reserve((2 * kBytes) / sizeof(ts::cplx));
-        const size_t at = (host.size() + 15) / 16 * 16;
+        const size_t at = (host.size() + kAlign - 1) / kAlign * kAlign;
         host.resize(at + entries);
         return at;
     }
