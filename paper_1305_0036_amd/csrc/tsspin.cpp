@@ -445,10 +445,14 @@ bool cone_candidate(ts_ctx *c, PlanEntry *pe, int T, int dtype, int mode, const 
     ts::ConePlan cp;
     double cost;
     int even = like ? like->cone_even : -1;
-    const size_t limit = 4 * pe->plan.sweeps.size() + 16;
     const double pp = (double)pe->plan.sweeps.size() * pingpong_sweep_us(dtype, T);
-    const double ppc = pp * std::ldexp(1.0, c->n - 27) + kLaunchUs * (double)pe->plan.sweeps.size();
+    const double scale = std::ldexp(1.0, c->n - 27);
+    const double ppc = pp * scale + kLaunchUs * (double)pe->plan.sweeps.size();
     const double bound = mode == 1 ? 0.95 * ppc : HUGE_VAL;
+    // a plan of more sweeps than the bound pays for, without stages, is not finished
+    size_t limit = 4 * pe->plan.sweeps.size() + 16;
+    if (mode == 1)
+        limit = std::min(limit, 1 + (size_t)(bound / ((dtype == TS_C128 ? 526.0 : 201.0) * scale + kLaunchUs)));
     if (!cone_windows(c, pe->plan.chain, T, kConeLowBits, dtype, c->cone_adv, limit, bound, &even, cp, &cost) ||
         cost < 0.0 || cost >= bound)
         return false;  // keep the ping-pong plan
