@@ -349,14 +349,16 @@ tsk::DiagArgs diag_args(const ts::DiagStep &d)
     return a;
 }
 
-// Light-cone plan of the same chain, kept when the cost model prefers it over the ping-pong
-// plan (mode 1) or whenever it fits the kernel (mode 2).  Model (fitted to kernel traces of
-// the xyz chain at N = 27, in microseconds for 2^27 amplitudes; within 4% at N = 27 and 30):
-// a light-cone sweep costs 526 + 30.3 per transpose + 40.1 per phase step + 11.3 per
-// spin-layer (complex128) or 201 + 8.3 + 41.5 + 11.9 (complex64): it is bound by latency,
-// vector instructions and LDS, not by HBM.  A ping-pong sweep moves the state once: see
-// pingpong_sweep_us.  Both scale with 2^(N-27); every launch adds about 8 us, which decides
-// at small N.
+// The light-cone form of a chain is taken when the cost model prefers it over the ping-pong plan
+// (mode 1) or whenever it fits the kernel (mode 2).  Model (fitted to kernel traces of the xyz
+// chain at N = 27, in microseconds for 2^27 amplitudes): a light-cone sweep costs 526 + 30.3 per
+// transpose + 40.1 per phase step + 11.3 per spin-layer (complex128) or 201 + 8.3 + 41.5 + 11.9
+// (complex64): it is bound by latency, vector instructions and LDS, not by HBM.  A ping-pong
+// sweep moves the state once: see pingpong_sweep_us.  Both scale with 2^(N-27); every launch adds
+// about 8 us, which decides at small N.  The traces are older than the phase products in place:
+// the complex128 step at N = 27 takes 14.0 ms where the model says 17.5, the complex64 step 10.8
+// (12.8), so the choice leans to the ping-pong form; and that is priced at the default width, also
+// where it runs narrow (resolve_tile).
 double pingpong_sweep_us(int dtype, int T)
 {
     // measured per sweep at N = 27 (complex64 T = 13, 14 and complex128 T = 13: N = 27-30)
@@ -3544,9 +3546,9 @@ extern "C" ts_status ts_create_batch(int32_t n_chains, const int32_t *n_spins, c
         b->chains.emplace_back(ch);
     }
     b->n = 0;
-    // batched classes keep the ping-pong sweeps unless asked (TSSPIN_CONE) or tuned otherwise:
-    // with many chains per launch the GPU is full and the light-cone sweeps, bound by vector
-    // instructions, measured slower on the 512-chain workload
+    // batched classes keep the ping-pong sweeps unless asked (TSSPIN_CONE) or tuned otherwise.
+    // (On the 512-chain workload the two forms measured alike when this default was set; with the
+    // present kernels tuning takes light-cone classes: 6.3 ms per recorded step against 8.4.)
     b->cone_mode = 0;
     if (const char *v = std::getenv("TSSPIN_CONE")) b->cone_mode = std::atoi(v);
     if (const char *v = std::getenv("TSSPIN_RESIDENT_TAB_BYTES")) b->resident_tab_bytes = (size_t)std::strtoull(v, nullptr, 10);

@@ -19,6 +19,11 @@ Subcommands:
              complex64 at the library's default width (one warm-up, one traced).
   run-adjoint   profiled workload: the N = 20 gradient chain, a 40-step adjoint (warm-up),
              then the 300-step adjoint and a 300-step forward run.
+  run-small     profiled workload: states of at most 24 spins, complex128: recorded chains of 9
+             and 12 spins, a ring of 16, chains of 19, 20 and 23, and seven observables of
+             a chain of 24.
+  resources     registers, scratch, LDS and waves of the sweep and reduction kernels, from the
+             compiler's kernel-resource-usage remarks (one compilation, no GPU).
   phase-split   from a kernel trace of run-dipolar: the traced step's sweeps with and
              without a phase step, their average durations and GB/s.
 
@@ -254,6 +259,69 @@ def cmd_run_adjoint(args):
     print(f"[profile] adjoint {1e3 * (t1 - t0):.1f} ms, forward {1e3 * (t2 - t1):.1f} ms", flush=True)
 
 
+def cmd_run_small(args):
+    sys.path.insert(0, ROOT)
+    import torch
+
+    from paper_1305_0036_amd import tsspin
+    from paper_1305_0036_amd import workloads as W
+
+    def state(n):
+        g = torch.Generator(device="cpu").manual_seed(n)
+        return torch.polar(torch.full((1 << n,), 2.0 ** (-n / 2), dtype=torch.float64),
+                           torch.rand(1 << n, dtype=torch.float64, generator=g) * 6.283).cuda()
+
+    for n, steps, record in ((9, 3, True), (12, 200, True), (19, 8, False), (20, 8, False), (23, 8, False)):
+        w = W.xyz_chain(n=n, nsteps=1, state=False)
+        H, x = tsspin.Hamiltonian(n, w.bonds, w.fields), state(n)
+        for _ in range(3):
+            H.evolve(x, w.dt, steps, 4, record=[("sz", 0), ("norm",)] if record else ())
+        torch.cuda.synchronize()
+        print(f"[profile] chain {n}", flush=True)
+    w = W.xyz_chain(n=16, nsteps=1, state=False)
+    H, x = tsspin.Hamiltonian(16, list(w.bonds) + [(0, 15, 1.0, 0.8, 0.6)], w.fields), state(16)
+    for _ in range(3):
+        H.evolve(x, w.dt, 20, 4)
+    torch.cuda.synchronize()
+    w = W.xyz_chain(n=24, nsteps=1, state=False)
+    H, x = tsspin.Hamiltonian(24, w.bonds, w.fields), state(24)
+    for _ in range(3):
+        H.expect(x, [("energy",), ("norm",), ("mz",), ("sz", 0), ("sx", 3), ("sy", 7), ("szsz", 0, 23)])
+    print("[profile] done", flush=True)
+
+
+def cmd_resources(args):
+    import re
+    import subprocess
+
+    from paper_1305_0036_amd import build as B
+
+    cmd = [B.hipcc(), "-O3", "-std=c++17", "-fPIC", f"--offload-arch={B.ARCH}", "-Xclang", "-target-feature",
+           "-Xclang", "-packed-fp32-ops", "-I", os.path.join(ROOT, "include"), "--cuda-device-only",
+           "-Rpass-analysis=kernel-resource-usage", "-c", os.path.join(B.CSRC, "kernels.hip"), "-o", os.devnull]
+    text = subprocess.run(cmd, capture_output=True, text=True, check=True).stderr
+    blocks = re.split(r"Function Name: ", text)[1:]
+    names = subprocess.run(["c++filt"], input="\n".join(b.split()[0] for b in blocks), capture_output=True,
+                           text=True, check=True).stdout.splitlines()
+    lines = ["# Registers, scratch, LDS and waves per SIMD of the kernels (gfx950, compiler's report)", "",
+             "Command (no GPU needed):", "", "```",
+             f"python3 -m paper_1305_0036_amd.profile_traffic resources --out {args.out}", "```", "",
+             "| kernel | VGPRs | scratch (bytes per lane) | static LDS (bytes) | waves per SIMD |", "|---|---|---|---|---|"]
+    want = ("cone_kernel<", "cone_rec_kernel<", "cone_batch_kernel<", "cone_pair", "resident_kernel<", "energy_kernel<",
+            "reduce_kernel<", "sweep_reg_kernel<double, 10, 3>", "sweep_reg_kernel<double, 12, 4>",
+            "sweep_reg_kernel<float, 13, 4>", "sweep_half_kernel<12")
+    for b, n in sorted(zip(blocks, names), key=lambda x: x[1]):
+        n = n.split("(")[0].replace("void ", "").replace("tsk::", "")
+        if not any(k in n for k in want):
+            continue
+        g = {k: re.search(k + r"[^:]*: (\d+)", b).group(1) for k in ("VGPRs", "ScratchSize", "LDS Size", "Occupancy")}
+        lines.append(f"| `{n}` | {g['VGPRs']} | {g['ScratchSize']} | {g['LDS Size']} | {g['Occupancy']} |")
+    lines += ["", "cone_kernel and cone_rec_kernel: the last number is the form (0 many workgroups, 1 up to one per "
+              "CU, 2 up to half as many).", "", f"Source hash of the kernels and planner: `{source_hash()}`.", ""]
+    with open(args.out, "w") as f:
+        f.write("\n".join(lines))
+
+
 def cmd_phase_split(args):
     rows = sorted(csv.DictReader(open(args.csv)), key=lambda r: int(r["Start_Timestamp"]))
     sw = [r for r in rows if "sweep" in r["Kernel_Name"]]
@@ -296,6 +364,9 @@ def main():
     sub.add_parser("run")
     sub.add_parser("run-dipolar")
     sub.add_parser("run-adjoint")
+    sub.add_parser("run-small")
+    r = sub.add_parser("resources")
+    r.add_argument("--out", required=True)
     ps = sub.add_parser("phase-split")
     ps.add_argument("--csv", required=True)
     ps.add_argument("--plan", required=True, help="the stdout of run-dipolar")
@@ -320,7 +391,7 @@ def main():
     args = ap.parse_args()
     {"run": cmd_run, "traffic": cmd_traffic, "stats": cmd_stats, "counters": cmd_counters,
      "run-dipolar": cmd_run_dipolar, "run-adjoint": cmd_run_adjoint,
-     "phase-split": cmd_phase_split}[args.cmd](args)
+     "run-small": cmd_run_small, "resources": cmd_resources, "phase-split": cmd_phase_split}[args.cmd](args)
 
 
 if __name__ == "__main__":
