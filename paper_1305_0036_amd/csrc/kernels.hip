@@ -1561,7 +1561,8 @@ __host__ __device__ constexpr size_t cone_tab_bytes(int n_phases)
 // of a step all at once) and a full buffer, or two (one barrier per transpose), shorten.  But
 // launches on other streams should run beside it, up to four (the hardware queues of a process):
 // kConeFew, of at most half as many workgroups as CUs, stays within half a CU; kConeMid (complex128,
-// up to one workgroup per CU) keeps the half buffer and three waves per SIMD.
+// up to one workgroup per CU) keeps the half buffer, and has the registers of three waves per SIMD
+// (it needs 113, as kConeMany: only the order of its phase products differs).
 // Eight fourth-order steps of a complex128 chain, us: N = 18 1140 as kConeFew and 1266 otherwise,
 // N = 19 1205 and 1336 (four streams at once 2730 and 3100); N = 20 as kConeMid 1465 (2290
 // on four streams), as kConeMany 1500 (2300), as kConeFew 1353 (3100).  Two full buffers in

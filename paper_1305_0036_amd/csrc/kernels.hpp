@@ -412,8 +412,8 @@ hipError_t launch_cone_pair(int dtype, int T, int RB, void *psi, void *lam, cons
 
 // Launches of at most kConeFewTiles workgroups (half the CUs: a second and a third launch of that
 // size on other streams then still run beside the first) run the form of the light-cone kernel that
-// takes half a CU per workgroup; complex128 ones of at most kConeMidTiles (one per CU) the form of
-// three workgroups per CU; larger ones that of four.
+// takes half a CU per workgroup; larger ones a form of four workgroups per CU, which forms a step's
+// phase products all at once (complex128 up to kConeMidTiles, one per CU) or four at a time.
 constexpr uint64_t kConeFewTiles = 128, kConeMidTiles = 256;
 // One light-cone sweep of n_tiles workgroups; `a` points to device memory and n_phases is its
 // n_phases (checked against the limit).  The phase tables that `a` names are read-only while
