@@ -3222,23 +3222,24 @@ static hipError_t launch_cone_k(typename Vec<R>::T *psi, const ConeArgs *a, uint
 
 template <typename R, int T>
 static hipError_t launch_cone_t(typename Vec<R>::T *psi, const ConeArgs *a, uint64_t n_tiles, int reverse,
-                                const ConeRec *rec, hipStream_t s)
+                                const ConeRec *rec, hipStream_t s, uint64_t few_tiles)
 {
-    if (n_tiles <= kConeFewTiles) return launch_cone_k<R, T, kConeFew>(psi, a, n_tiles, reverse, rec, s);
+    if (n_tiles <= few_tiles) return launch_cone_k<R, T, kConeFew>(psi, a, n_tiles, reverse, rec, s);
     if constexpr (sizeof(R) == 8)
         if (n_tiles <= kConeMidTiles) return launch_cone_k<R, T, kConeMid>(psi, a, n_tiles, reverse, rec, s);
     return launch_cone_k<R, T, kConeMany>(psi, a, n_tiles, reverse, rec, s);
 }
 
 static hipError_t launch_cone_any(int dtype, int T, int RB, void *psi, const ConeArgs *a, int n_phases,
-                                  uint64_t n_tiles, int reverse, const ConeRec *rec, hipStream_t s)
+                                  uint64_t n_tiles, int reverse, const ConeRec *rec, hipStream_t s,
+                                  uint64_t few_tiles = kConeFewTiles)
 {
     if (!a || RB != 4 || n_phases < 0 || n_phases > kConePhases || n_tiles == 0 || n_tiles > 0x7fffffffull)
         return hipErrorInvalidValue;
 #define TS_CONE_CASE(TT)                                                                              \
     if (T == TT)                                                                                      \
-        return dtype == 0 ? launch_cone_t<double, TT>(static_cast<double2 *>(psi), a, n_tiles, reverse, rec, s) \
-                          : launch_cone_t<float, TT>(static_cast<float2 *>(psi), a, n_tiles, reverse, rec, s);
+        return dtype == 0 ? launch_cone_t<double, TT>(static_cast<double2 *>(psi), a, n_tiles, reverse, rec, s, few_tiles) \
+                          : launch_cone_t<float, TT>(static_cast<float2 *>(psi), a, n_tiles, reverse, rec, s, few_tiles);
     TS_CONE_CASE(11)
     TS_CONE_CASE(12)
 #undef TS_CONE_CASE
@@ -3246,9 +3247,9 @@ static hipError_t launch_cone_any(int dtype, int T, int RB, void *psi, const Con
 }
 
 hipError_t launch_cone(int dtype, int T, int RB, void *psi, const ConeArgs *a, int n_phases,
-                       uint64_t n_tiles, int reverse, hipStream_t s)
+                       uint64_t n_tiles, int reverse, hipStream_t s, uint64_t few_tiles)
 {
-    return launch_cone_any(dtype, T, RB, psi, a, n_phases, n_tiles, reverse, nullptr, s);
+    return launch_cone_any(dtype, T, RB, psi, a, n_phases, n_tiles, reverse, nullptr, s, few_tiles);
 }
 
 hipError_t launch_cone_rec(int dtype, int T, int RB, void *psi, const ConeArgs *a, int n_phases,

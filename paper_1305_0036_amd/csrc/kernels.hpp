@@ -415,11 +415,17 @@ hipError_t launch_cone_pair(int dtype, int T, int RB, void *psi, void *lam, cons
 // takes half a CU per workgroup; larger ones a form of four workgroups per CU, which forms a step's
 // phase products all at once (complex128 up to kConeMidTiles, one per CU) or four at a time.
 constexpr uint64_t kConeFewTiles = 128, kConeMidTiles = 256;
+// The complex128 forward run of ts_adjoint takes the form of few tiles up to one workgroup per CU:
+// the call returns when it is done, and its reverse sweeps of psi and lambda take half a CU each
+// anyway (N = 20, 40 steps: 22.7 against 23.3 ms; 20 steps in two threads at once 19.3 ms, with
+// one workgroup per CU 22.2; complex64 gains 1% alone and loses 3% in four threads).
+constexpr uint64_t kConeAdjointFewTiles = 256;
 // One light-cone sweep of n_tiles workgroups; `a` points to device memory and n_phases is its
 // n_phases (checked against the limit).  The phase tables that `a` names are read-only while
 // the sweep runs (the kernel reads them through the scalar data cache).
 hipError_t launch_cone(int dtype, int T, int RB, void *psi, const ConeArgs *a, int n_phases,
-                       uint64_t n_tiles, int reverse, hipStream_t s);
+                       uint64_t n_tiles, int reverse, hipStream_t s,
+                       uint64_t few_tiles = kConeFewTiles);
 // The same sweep with the observables of `rec` accumulated from the stored tile (one row of
 // rec.partials per workgroup).
 hipError_t launch_cone_rec(int dtype, int T, int RB, void *psi, const ConeArgs *a, int n_phases,

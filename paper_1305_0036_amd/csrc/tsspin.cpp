@@ -1633,7 +1633,8 @@ ts_status run_resident_records(ts_ctx *c, int dtype, int T, int order, double dt
 // vector accumulates into c->cone_partials, column = position in *fuse; *fused is set when
 // this plan did so (light-cone form), and left alone otherwise.
 ts_status run_plan(ts_ctx *c, PlanEntry *pe, int dtype, void *const *psi, int n_psi,
-                   hipStream_t stream, const std::vector<tsk::ObsDev> *fuse = nullptr, bool *fused = nullptr)
+                   hipStream_t stream, const std::vector<tsk::ObsDev> *fuse = nullptr, bool *fused = nullptr,
+                   uint64_t few_tiles = tsk::kConeFewTiles)
 {
     const ts::Plan &P = pe->plan;
     const int n = c->n;
@@ -1674,7 +1675,7 @@ ts_status run_plan(ts_ctx *c, PlanEntry *pe, int dtype, void *const *psi, int n_
                                                 pe->cone_host[k].n_phases, tiles, (int)(k & 1), rec, stream));
                 else
                     TS_HIP(tsk::launch_cone(dtype, pe->cone_plan.T, c->reg_bits[dtype], psi[v], dev + k,
-                                            pe->cone_host[k].n_phases, tiles, (int)(k & 1), stream));
+                                            pe->cone_host[k].n_phases, tiles, (int)(k & 1), stream, few_tiles));
             }
         }
         if (fuse) c->cone_partial_rows = (int64_t)tiles;
@@ -1698,7 +1699,8 @@ constexpr int64_t kChunkSteps = 32;
 // fuse/fused: as for run_plan, applied to the last plan of the run.
 ts_status run_steps(ts_ctx *c, int dtype, int T, int order, double dt, int64_t steps,
                     void *const *psi, int n_psi, hipStream_t s,
-                    const std::vector<tsk::ObsDev> *fuse = nullptr, bool *fused = nullptr)
+                    const std::vector<tsk::ObsDev> *fuse = nullptr, bool *fused = nullptr,
+                    uint64_t few_tiles = tsk::kConeFewTiles)
 {
     while (steps > 0) {
         const int64_t k = std::min(steps, kChunkSteps);
@@ -1706,7 +1708,7 @@ ts_status run_steps(ts_ctx *c, int dtype, int T, int order, double dt, int64_t s
         ts_status st = build_plan(c, dtype, T, order, dt, k, &pe);
         if (st != TS_OK) return st;
         const bool tail = steps == k;
-        st = run_plan(c, pe, dtype, psi, n_psi, s, tail ? fuse : nullptr, tail ? fused : nullptr);
+        st = run_plan(c, pe, dtype, psi, n_psi, s, tail ? fuse : nullptr, tail ? fused : nullptr, few_tiles);
         if (st != TS_OK) return st;
         steps -= k;
     }
@@ -3115,7 +3117,8 @@ extern "C" ts_status ts_adjoint(ts_ctx *ctx, const void *psi0, ts_dtype dtype, d
 
     // forward: psi(T)
     TS_HIP(hipMemcpyAsync(psi, psi0, bytes, hipMemcpyDeviceToDevice, s));
-    st = run_steps(ctx, dtype, Tdef, order, dt, nsteps, vecs, 1, s);
+    st = run_steps(ctx, dtype, Tdef, order, dt, nsteps, vecs, 1, s, nullptr, nullptr,
+                   dtype == TS_C128 ? tsk::kConeAdjointFewTiles : tsk::kConeFewTiles);
     if (st != TS_OK) return st;
     // loss and lambda = O psi(T)
     std::vector<tsk::ObsDev> od(1);
