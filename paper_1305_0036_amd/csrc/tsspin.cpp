@@ -225,6 +225,7 @@ ts_status alloc(DevBuf &b, size_t bytes)
     }
     hipError_t e = hipMalloc(&b.p, bytes);
     if (e != hipSuccess) {
+        (void)hipGetLastError();   // or the next launch reports it
         b.p = nullptr;
         return fail(e == hipErrorOutOfMemory ? TS_ENOMEM : TS_EDEVICE,
                     std::string("hipMalloc: ") + hipGetErrorString(e));
@@ -2234,10 +2235,7 @@ ts_status resident_tables(ts_ctx *ctx, BatchProgram *bp, const std::string &key,
     }
     *tab = std::make_shared<DevBuf>();
     ts_status st;
-    while ((st = alloc(**tab, *group * per_chain)) == TS_ENOMEM && *group > 1) {
-        (void)hipGetLastError();
-        *group = (*group + 1) / 2;
-    }
+    while ((st = alloc(**tab, *group * per_chain)) == TS_ENOMEM && *group > 1) *group = (*group + 1) / 2;
     return st;
 }
 

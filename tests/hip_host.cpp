@@ -15,6 +15,7 @@ std::map<std::string, long> launches;        // by mangled name
 std::map<void *, size_t> blocks;
 long allocs, uploads, failed;
 size_t held, peak, limit = ~(size_t)0;
+hipError_t last = hipSuccess;                // until hipGetLastError takes it
 struct { dim3 g, b; size_t lds; hipStream_t s; } conf;
 }
 
@@ -52,7 +53,7 @@ hipError_t hipLaunchKernel(const void *f, dim3 g, dim3 b, void **, size_t, hipSt
 hipError_t hipMalloc(void **p, size_t n)
 {
     *p = nullptr;
-    if (n > limit || held > limit - n) { ++failed; return hipErrorOutOfMemory; }
+    if (n > limit || held > limit - n) { ++failed; return last = hipErrorOutOfMemory; }
     *p = calloc(1, n ? n : 1);
     blocks[*p] = n;
     held += n;
@@ -94,6 +95,6 @@ hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) { *n = 2; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void **p, const void *) { static void *m = calloc(1, 1 << 22); *p = m; return hipSuccess; }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() { const hipError_t e = last; last = hipSuccess; return e; }
 const char *hipGetErrorString(hipError_t e) { return e == hipErrorOutOfMemory ? "out of memory" : "error"; }
 }

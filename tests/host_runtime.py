@@ -171,5 +171,15 @@ def tuner_widths(h, n, dtype):
     return {"untuned": [c.value for c in cfg[:2]], "timed": h.launches(f"sweep_reg_kernelIdLi{cfg[0].value}ELi{cfg[1].value}E")}
 
 
+def call_after_a_refused_allocation(h, n, dtype):
+    """The result of a call without memory for its tables, and of the same call with it."""
+    ctx, psi = h.system(n, ring=True), (C.c_void_p * 1)(4096)
+    args = (ctx, psi, 1, dtype, C.c_double(0.05), C.c_int64(2), 4, None, 0, 1, None, None)
+    h.rt.host_limit(C.c_size_t(0))
+    first = h.lib.ts_evolve(*args)
+    h.rt.host_limit(C.c_size_t(1 << 40))
+    return [first, h.lib.ts_evolve(*args)]
+
+
 if __name__ == "__main__":
     print(json.dumps(globals()[sys.argv[1]](Host(), *json.loads(sys.argv[2]))))

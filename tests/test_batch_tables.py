@@ -1,6 +1,7 @@
 """Device memory of a batch's phase tables, on the host-only runtime (no GPU needed): programs of
 the same steps share them, all programs together keep at most 4 GiB and their groups, and a device
-without room for a class's tables makes the groups smaller, not the call fail."""
+without room for a class's tables makes the groups smaller, not the call fail.  A refused allocation
+is not reported by the next call's launches."""
 from __future__ import annotations
 
 import pytest
@@ -37,3 +38,9 @@ def test_groups_of_chains(tmp_path, dtype):
 def test_short_of_memory(tmp_path, dtype):
     got = host_runtime.run(tmp_path, "batch_short_of_memory", 12, 200, dtype, 100 * CHAIN[dtype])
     assert got["rc"] == 0 and got["failed"] > 0
+
+
+@pytest.mark.parametrize("dtype", [host_runtime.C128, host_runtime.C64])
+@pytest.mark.parametrize("n", [5, 16, 20])
+def test_call_after_a_refused_allocation(tmp_path, n, dtype):
+    assert host_runtime.run(tmp_path, "call_after_a_refused_allocation", n, dtype) == [-2, 0]
