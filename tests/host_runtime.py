@@ -112,15 +112,15 @@ def first_call(h, n, dtype, steps):
 
 
 def narrow_first_call(h, n):
-    """Least time of the first call of a ring at its own width over that at width 12."""
+    """Least processor time of the first call of a ring at its own width over that at width 12."""
     best = {0: 1e9, 12: 1e9}
     for _ in range(25):
         for width in best:
             ctx = h.system(n, ring=True)
             h.ok(h.lib.ts_set_tile_bits(ctx, C128, width))
-            t = time.perf_counter()
+            t = time.thread_time()
             h.evolve(ctx, C128, 8)
-            best[width] = min(best[width], time.perf_counter() - t)
+            best[width] = min(best[width], time.thread_time() - t)
             h.ok(h.lib.ts_destroy(ctx))
     return {"ratio": best[0] / best[12]}
 
